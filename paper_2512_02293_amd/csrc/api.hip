@@ -56,7 +56,7 @@ struct vi_ctx {
   DevPlan dplan{};
   WinDev* d_win = nullptr;         // device window table (inside d_plan)
   std::vector<char> win_on_dev;    // bytes d_win holds (empty: not known), so an unchanged table is not sent again
-  int attr_kmax = -1;
+  int attr_kmax = -1, attr_cond = -1;
   // autotuning
   bool autotune = false;
   double tol = 0.0;                // tolerance stop of the solves (0: off)
@@ -141,10 +141,10 @@ vi_status check_opts(vi_ctx* ctx, const vi_opts* o) {
 }
 
 // Shape signature: everything the plan depends on (sizes and the frame graphs).
-std::vector<int32_t> plan_signature(const std::vector<WinIn>& wins, bool bias_global) {
+std::vector<int32_t> plan_signature(const std::vector<WinIn>& wins, bool use_imu, bool bias_global) {
   std::vector<int32_t> s;
   s.push_back((int32_t)wins.size());
-  s.push_back(bias_global ? 1 : 0);
+  s.push_back((use_imu ? 2 : 0) | (bias_global ? 1 : 0));
   for (const WinIn& in : wins) {
     s.push_back(in.st->n_kf);
     s.push_back(in.cam->H);
@@ -175,7 +175,7 @@ std::vector<int32_t> plan_signature(const std::vector<WinIn>& wins, bool bias_gl
 // ---------------------------------------------------------------------------
 struct Coupling {
   int a, b;
-  bool full;   // all unknowns of both keyframes coupled (else only the 6 pose unknowns at the head of each block)
+  bool full_a, full_b;   // all unknowns of that keyframe coupled (else only the 6 pose unknowns at the head of its block)
 };
 
 std::vector<int> rcm_order(int N, const std::vector<std::vector<int>>& adj) {
@@ -243,20 +243,77 @@ std::vector<int> rcm_order(int N, const std::vector<std::vector<int>>& adj) {
   return order;
 }
 
-// first nonzero scalar column of each scalar row of S (lower triangle) with
-// keyframe a at block position pos[a]
-void scalar_envelope(int N, int PD, const std::vector<Coupling>& cpl, const std::vector<int>& pos,
+// first nonzero scalar column of each scalar row of S (lower triangle), the
+// dim[a] unknowns of keyframe a starting at row off[a]
+void scalar_envelope(const std::vector<int>& dim, const std::vector<Coupling>& cpl, const std::vector<int>& off,
                      std::vector<int>& fcs) {
-  fcs.assign((size_t)N * PD, 0);
-  for (int a = 0; a < N; ++a)
-    for (int r = 0; r < PD; ++r) fcs[(size_t)pos[a] * PD + r] = pos[a] * PD;
+  int n = 0;
+  for (int d : dim) n += d;
+  fcs.assign(n, 0);
+  for (size_t a = 0; a < dim.size(); ++a)
+    for (int r = 0; r < dim[a]; ++r) fcs[off[a] + r] = off[a];
   for (const Coupling& c : cpl) {
-    int qa = pos[c.a], qb = pos[c.b];
-    if (qa == qb) continue;
-    if (qa < qb) std::swap(qa, qb);
-    const int rows = c.full ? PD : 6;
-    for (int r = 0; r < rows; ++r) fcs[(size_t)qa * PD + r] = std::min(fcs[(size_t)qa * PD + r], qb * PD);
+    const bool up = off[c.a] > off[c.b];
+    const int hi = up ? c.a : c.b, lo = up ? c.b : c.a;
+    const int rows = (up ? c.full_a : c.full_b) ? dim[hi] : 6;
+    for (int r = 0; r < rows; ++r) fcs[off[hi] + r] = std::min(fcs[off[hi] + r], off[lo]);
   }
+}
+
+// Separator keyframes of a window of N keyframes (see kCondSpan): about every
+// kCondSpan, more where the padding of the last tile takes their unknowns
+std::vector<char> cond_separators(int N, bool bias_global) {
+  std::vector<char> sep(N, 0);
+  int nseg = (N + kCondSpan) / (kCondSpan + 1);
+  const int n0 = 6 * N + (bias_global ? kCondNV : 0);
+  auto tiles = [&](int segs) { return (n0 + kCondNV * (segs - 1) + kCholNB - 1) / kCholNB; };
+  while (tiles(nseg + 1) == tiles(nseg) && (N - nseg) / (nseg + 1) >= kCondMinLen) ++nseg;
+  for (int j = 1; j < nseg; ++j) sep[(size_t)((long long)j * N / nseg)] = 1;
+  if (bias_global) sep[N - 1] = 1;
+  return sep;
+}
+
+// Segments between the separators and the sizes that go with them.
+struct CondLayout {
+  std::vector<SegDev> segs;
+  int n = 0;                 // unknowns of the reduced system
+  size_t doubles = 0;
+};
+
+CondLayout cond_layout(int N, bool bias_global) {
+  CondLayout C;
+  const std::vector<char> sep = cond_separators(N, bias_global);
+  for (char s : sep) C.n += s ? 15 : 6;
+  for (int a = 0; a < N; ++a) {
+    if (sep[a]) continue;
+    int b = a;
+    while (b + 1 < N && !sep[b + 1]) ++b;
+    SegDev S{};
+    S.a = a;
+    S.b = b;
+    S.k0 = std::max(a - 1, 0);
+    S.k1 = std::min(b + 1, N - 1);
+    S.nc = 6 * (S.k1 - S.k0 + 1);
+    S.vl = S.vr = S.gb = -1;
+    if (a > 0) { S.vl = S.nc; S.nc += kCondNV; }
+    if (b < N - 1) { S.vr = S.nc; S.nc += kCondNV; }
+    if (bias_global) {
+      if (b + 1 == N - 1) S.gb = S.vr + 3;
+      else { S.gb = S.nc; S.nc += 6; }
+    }
+    S.ld = (S.nc + 16) / 16 * 16;
+    S.nf = S.k1 - S.k0;
+    const int len = b - a + 1;
+    S.y_off = (int64_t)C.doubles;
+    C.doubles += (size_t)kCondNV * len * S.ld;
+    S.l_off = (int64_t)C.doubles;
+    C.doubles += (size_t)162 * len;
+    S.g_off = (int64_t)C.doubles;
+    C.doubles += (size_t)S.ld * S.ld;
+    C.segs.push_back(S);
+    a = b;
+  }
+  return C;
 }
 
 // tile envelope (nblk + 1 entries, the last one the right-hand-side row), the
@@ -286,7 +343,7 @@ Envelope tile_envelope(const std::vector<int>& fcs, int n, int nblk) {
   return E;
 }
 
-vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool bias_global = false) {
+vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool use_imu, bool bias_global) {
   P = Plan();
   const int nw = (int)wins.size();
   // pose-graph adjustment (one window): 7 unknowns per keyframe, 7x7 blocks,
@@ -330,8 +387,9 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
     P.hw_max = std::max(P.hw_max, W.HW);
   }
   P.N = kf;
-  P.kf_pos.assign(P.N, 0);
-  P.kf_at.assign(P.N, 0);
+  P.kf_off.assign(P.N, 0);
+  P.kf_seg.assign((size_t)2 * P.N, -1);
+  P.f_seg.assign(std::max(fa, 1), -1);
   P.E = ed;
   P.F = fa;
   P.pix_total = pix;
@@ -405,9 +463,21 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
   // per window: reduced system and gather lists of its assembly.  Pose block
   // (a, b) <- Z blocks of every source whose touched set contains a and b.
   size_t A_off = 0, L_off = 0, x_off = 0;
+  size_t A_cap[2] = {0, 0}, L_cap[2] = {0, 0}, x_cap[2] = {0, 0}, f_cap[2] = {0, 0}, c_cap[2] = {0, 0},
+         s_cap[2] = {0, 0};
   for (int w = 0; w < nw; ++w) {
     WinDev& W = P.win[w];
-    W.n = PD * W.N;
+    // unknowns per keyframe that stay in the reduced system
+    std::vector<int> dim(W.N, pg ? 7 : 6);
+    CondLayout cond;
+    if (!pg && use_imu) {
+      cond = cond_layout(W.N, bias_global);
+      const std::vector<char> sep = cond_separators(W.N, bias_global);
+      for (int a = 0; a < W.N; ++a)
+        if (sep[a]) dim[a] = 15;
+    }
+    W.n = 0;
+    for (int d : dim) W.n += d;
     W.npad = (W.n + kCholNB - 1) / kCholNB * kCholNB;
     W.nblk = W.npad / kCholNB;
     W.A_off = (long long)A_off;
@@ -440,19 +510,21 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
       }
     }
     // couplings of S: the vision terms couple only the 6 pose unknowns at the
-    // head of each keyframe's 15 in the visual-inertial layout (all 7 in the
-    // pose graph); the inertial factors the full blocks of consecutive keyframes
+    // head of each keyframe's block (all 7 in the pose graph); a segment couples
+    // all of its columns (poses of the segment and its neighbours, V of the
+    // separators beside it)
     std::vector<Coupling> cpl;
     std::vector<std::vector<int>> adj(W.N);
     for (int a = 0; a < W.N; ++a)
       for (int b = 0; b < a; ++b)
-        if (!items[(size_t)a * W.N + b].empty()) cpl.push_back({a, b, pg});
-    if (!pg)
-      for (int a = 0; a + 1 < W.N; ++a) cpl.push_back({a + 1, a, true});
+        if (!items[(size_t)a * W.N + b].empty()) cpl.push_back({a, b, pg, pg});
+    for (const SegDev& S : cond.segs)
+      for (int a = S.k0; a <= S.k1; ++a)
+        for (int b = S.k0; b < a; ++b) cpl.push_back({a, b, true, true});
     // one bias for the window: it sits in the last keyframe's slot and couples
     // with every keyframe that an inertial factor touches
-    if (!pg && bias_global)
-      for (int a = 0; a + 2 < W.N; ++a) cpl.push_back({W.N - 1, a, true});
+    if (!pg && use_imu && bias_global)
+      for (int a = 0; a + 1 < W.N; ++a) cpl.push_back({W.N - 1, a, true, true});
     for (const Coupling& c : cpl) {
       adj[c.a].push_back(c.b);
       adj[c.b].push_back(c.a);
@@ -464,23 +536,63 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
     // natural order unless the reverse Cuthill-McKee order lowers the work of
     // the factorisation path this window takes (tile updates of the dataflow
     // path, the band of the one-workgroup path)
-    std::vector<int> pos(W.N), fcs;
-    for (int a = 0; a < W.N; ++a) pos[a] = a;
-    scalar_envelope(W.N, PD, cpl, pos, fcs);
+    std::vector<int> off(W.N), fcs;
+    for (int a = 0, r = 0; a < W.N; r += dim[a++]) off[a] = r;
+    scalar_envelope(dim, cpl, off, fcs);
     Envelope env = tile_envelope(fcs, W.n, W.nblk);
-    const std::vector<int> rcm = rcm_order(W.N, adj);
-    std::vector<int> pos2(W.N);
-    for (int q = 0; q < W.N; ++q) pos2[rcm[q]] = q;
-    scalar_envelope(W.N, PD, cpl, pos2, fcs);
-    Envelope env2 = tile_envelope(fcs, W.n, W.nblk);
     const bool small_path = W.npad <= kCholSmallMaxNpad;
-    if (small_path ? env2.band < env.band : env2.work < env.work) {
-      pos.swap(pos2);
-      env = std::move(env2);
+    if (env.band > 0) {
+      const std::vector<int> rcm = rcm_order(W.N, adj);
+      std::vector<int> off2(W.N);
+      for (int q = 0, r = 0; q < W.N; r += dim[rcm[q++]]) off2[rcm[q]] = r;
+      scalar_envelope(dim, cpl, off2, fcs);
+      Envelope env2 = tile_envelope(fcs, W.n, W.nblk);
+      if (small_path ? env2.band < env.band : env2.work < env.work) {
+        off.swap(off2);
+        env = std::move(env2);
+      }
     }
+    P.row_map.resize(x_off, -1);
     for (int a = 0; a < W.N; ++a) {
-      P.kf_pos[W.kf_base + a] = pos[a];
-      P.kf_at[W.kf_base + pos[a]] = a;
+      P.kf_off[W.kf_base + a] = off[a];
+      for (int r = 0; r < dim[a]; ++r) P.row_map[(size_t)W.x_off + off[a] + r] = (a << 8) | r;
+    }
+    // segments: offsets of this window's pieces, the segments of each pose and factor
+    W.seg_base = (int)P.segs.size();
+    W.nseg = (int)cond.segs.size();
+    for (SegDev S : cond.segs) {
+      const int id = (int)P.segs.size();
+      S.w = w;
+      S.y_off += (int64_t)P.cond_size;
+      S.l_off += (int64_t)P.cond_size;
+      S.g_off += (int64_t)P.cond_size;
+      for (int a = S.k0; a <= S.k1; ++a) {
+        int32_t* ks = &P.kf_seg[2 * (size_t)(W.kf_base + a)];
+        (ks[0] < 0 ? ks[0] : ks[1]) = id;
+      }
+      for (int f = S.k0; f < S.k1; ++f) P.f_seg[W.f_base + f] = id;
+      const int T = S.ld / 16;
+      for (int t = 0; t < T * (T + 1) / 2; t += kSegGramTiles) {
+        P.gram_map.push_back(id);
+        P.gram_map.push_back(t);
+      }
+      P.cond_len = std::max(P.cond_len, S.b - S.a + 1);
+      P.segs.push_back(S);
+    }
+    if (!pg) {
+      // every option set of these windows fits one workspace: the larger of
+      // the reduced systems with and without eliminated unknowns
+      for (int g = 0; g < 2; ++g) {
+        const CondLayout C = cond_layout(W.N, g != 0);
+        const size_t np = (size_t)(C.n + kCholNB - 1) / kCholNB * kCholNB;
+        A_cap[g] += (np + kCholNB) * np;
+        L_cap[g] += np * kCholNB;
+        x_cap[g] += np;
+        f_cap[g] += (np / kCholNB + 2) * (np / kCholNB);
+        c_cap[g] += C.doubles;
+        s_cap[g] += C.segs.size();
+      }
+      P.cond_size += cond.doubles;
     }
     W.band = env.band;
     W.fc_off = (int)P.chol_fc.size();
@@ -529,9 +641,14 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
       P.chol_tiles.push_back(c);
     }
   P.n_bs = (int)(P.chol_tiles.size() / 2) - P.n_tickets;
-  P.A_size = A_off;
-  P.Linv_size = L_off;
-  P.x_size = x_off;
+  P.row_map.resize(x_off, -1);
+  if (P.gram_map.empty()) P.gram_map.push_back(0);
+  P.A_size = std::max({A_off, A_cap[0], A_cap[1]});
+  P.Linv_size = std::max({L_off, L_cap[0], L_cap[1]});
+  P.x_size = std::max({x_off, x_cap[0], x_cap[1]});
+  P.flags_size = std::max({P.flags_size, f_cap[0], f_cap[1]});
+  P.cond_size = std::max({P.cond_size, c_cap[0], c_cap[1]});
+  P.seg_cap = std::max({P.segs.size(), s_cap[0], s_cap[1]});
   return VI_OK;
 }
 
@@ -539,8 +656,10 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
 // keyframe * unknowns-per-keyframe + unknown
 int natural_coord(const Plan& P, int w, int c) {
   const WinDev& W = P.win[w];
+  if (c >= kNaturalDetail) return c - kNaturalDetail;
   if (c < 0 || c >= W.n) return c;
-  return P.kf_at[W.kf_base + c / P.pdim] * P.pdim + c % P.pdim;
+  const int32_t m = P.row_map[(size_t)W.x_off + c];
+  return (m >> 8) * P.pdim + (m & 255);
 }
 
 void set_range(Plan& P, int range) {
@@ -602,6 +721,8 @@ Work do_carve(const Plan& P, void* base, size_t* bytes) {
   w.x = c.take<double>(P.x_size);
   w.trace = c.take<double>((size_t)P.n_win * kTraceLen);
   w.rcost = c.take<double>((size_t)std::max(P.R, 1));
+  w.cond = c.take<double>(P.cond_size);
+  w.seg_cnt = c.take<int32_t>(P.seg_cap);
   if (bytes) *bytes = c.off;
   return w;
 }
@@ -609,12 +730,21 @@ Work do_carve(const Plan& P, void* base, size_t* bytes) {
 // Upload the int tables; the window table at the front is refreshed per call.
 vi_status upload_plan(vi_ctx* ctx) {
   const Plan& P = ctx->plan;
-  const std::vector<int32_t>* parts[] = {&P.ii, &P.jj, &P.win_of_kf, &P.win_of_f, &P.src_off, &P.src_edges,
-                                         &P.gram_off, &P.z_off, &P.zb_off, &P.pair_off, &P.pair_z, &P.pair_zb,
-                                         &P.chol_tiles, &P.rel_ii, &P.rel_jj, &P.rel_z, &P.rel_zb,
-                                         &P.kf_pos, &P.kf_at, &P.chol_fc};
+  std::vector<int32_t> segs(P.segs.size() * (sizeof(SegDev) / 4));
+  if (!segs.empty()) std::memcpy(segs.data(), P.segs.data(), segs.size() * 4);
+  DevPlan& D = ctx->dplan;
+  const int32_t* dsegs = nullptr;
+  // each table and the device pointer that receives its place
+  struct Part { const std::vector<int32_t>* v; const int32_t** dst; };
+  const Part parts[] = {{&P.ii, &D.ii}, {&P.jj, &D.jj}, {&P.win_of_kf, &D.win_of_kf}, {&P.win_of_f, &D.win_of_f},
+                        {&P.src_off, &D.src_off}, {&P.src_edges, &D.src_edges}, {&P.gram_off, &D.gram_off},
+                        {&P.z_off, &D.z_off}, {&P.zb_off, &D.zb_off}, {&P.pair_off, &D.pair_off},
+                        {&P.pair_z, &D.pair_z}, {&P.pair_zb, &D.pair_zb}, {&P.chol_tiles, &D.chol_tiles},
+                        {&P.rel_ii, &D.rel_ii}, {&P.rel_jj, &D.rel_jj}, {&P.rel_z, &D.rel_z}, {&P.rel_zb, &D.rel_zb},
+                        {&P.kf_off, &D.kf_off}, {&P.row_map, &D.row_map}, {&P.chol_fc, &D.chol_fc},
+                        {&P.kf_seg, &D.kf_seg}, {&P.f_seg, &D.f_seg}, {&P.gram_map, &D.gram_map}, {&segs, &dsegs}};
   size_t total = align256(sizeof(WinDev) * P.n_win);
-  for (auto* v : parts) total += align256(std::max<size_t>(v->size(), 1) * sizeof(int32_t));
+  for (const Part& p : parts) total += align256(std::max<size_t>(p.v->size(), 1) * sizeof(int32_t));
   if (total > ctx->d_plan_cap) {
     if (ctx->d_plan) HIPCHK(ctx, hipFree(ctx->d_plan));
     ctx->d_plan = nullptr;
@@ -623,23 +753,16 @@ vi_status upload_plan(vi_ctx* ctx) {
   }
   std::vector<char> host(total, 0);
   size_t off = align256(sizeof(WinDev) * P.n_win);
-  const int32_t* dptr[20];
-  int idx = 0;
-  for (auto* v : parts) {
-    if (!v->empty()) std::memcpy(host.data() + off, v->data(), v->size() * sizeof(int32_t));
-    dptr[idx++] = (const int32_t*)(ctx->d_plan + off);
-    off += align256(std::max<size_t>(v->size(), 1) * sizeof(int32_t));
+  for (const Part& p : parts) {
+    if (!p.v->empty()) std::memcpy(host.data() + off, p.v->data(), p.v->size() * sizeof(int32_t));
+    *p.dst = (const int32_t*)(ctx->d_plan + off);
+    off += align256(std::max<size_t>(p.v->size(), 1) * sizeof(int32_t));
   }
+  D.segs = (const SegDev*)dsegs;
   ctx->win_on_dev.clear();
   HIPCHK(ctx, hipMemcpy(ctx->d_plan, host.data(), total, hipMemcpyHostToDevice));
-  DevPlan& D = ctx->dplan;
   ctx->d_win = (WinDev*)ctx->d_plan;
   D.win = ctx->d_win;
-  D.ii = dptr[0]; D.jj = dptr[1]; D.win_of_kf = dptr[2]; D.win_of_f = dptr[3]; D.src_off = dptr[4];
-  D.src_edges = dptr[5]; D.gram_off = dptr[6]; D.z_off = dptr[7]; D.zb_off = dptr[8];
-  D.pair_off = dptr[9]; D.pair_z = dptr[10]; D.pair_zb = dptr[11]; D.chol_tiles = dptr[12];
-  D.rel_ii = dptr[13]; D.rel_jj = dptr[14]; D.rel_z = dptr[15]; D.rel_zb = dptr[16];
-  D.kf_pos = dptr[17]; D.kf_at = dptr[18]; D.chol_fc = dptr[19];
   return VI_OK;
 }
 
@@ -652,11 +775,11 @@ vi_status ensure_status(vi_ctx* ctx, int n) {
   return VI_OK;
 }
 
-vi_status ensure_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, bool bias_global = false) {
-  std::vector<int32_t> sig = plan_signature(wins, bias_global);
+vi_status ensure_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, bool use_imu, bool bias_global) {
+  std::vector<int32_t> sig = plan_signature(wins, use_imu, bias_global);
   if (ctx->have_plan && sig == ctx->plan_sig) return VI_OK;
   Plan P;
-  vi_status s = build_plan(ctx, wins, P, bias_global);
+  vi_status s = build_plan(ctx, wins, P, use_imu, bias_global);
   if (s != VI_OK) return s;
   set_range(P, default_range(P));
   ctx->plan = std::move(P);
@@ -668,10 +791,11 @@ vi_status ensure_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, bool bias_glo
   if (s != VI_OK) return s;
   ctx->have_plan = true;
   ctx->plan_version++;
-  if (ctx->plan.kmax > ctx->attr_kmax) {
-    step_set_attributes(ctx->plan.kmax);
+  if (ctx->plan.kmax > ctx->attr_kmax || ctx->plan.cond_len > ctx->attr_cond) {
+    ctx->attr_kmax = std::max(ctx->attr_kmax, ctx->plan.kmax);
+    ctx->attr_cond = std::max(ctx->attr_cond, ctx->plan.cond_len);
+    step_set_attributes(ctx->attr_kmax, ctx->attr_cond);
     pg_set_attributes();
-    ctx->attr_kmax = ctx->plan.kmax;
   }
   return VI_OK;
 }
@@ -749,7 +873,7 @@ vi_status autotune_range(vi_ctx* ctx, const Work& w, const OptsDev& od) {
   hipStream_t sp = ctx->priv;
   hipEvent_t ev[kNumStages + 1];
   for (auto& e : ev) HIPCHK(ctx, hipEventCreate(&e));
-  launch_reset_status(sp, ctx->status, P.n_win);
+  launch_reset_status(sp, ctx->status, P.n_win, w.seg_cnt, (int)P.segs.size());
   if (od.use_imu) launch_imu_info(sp, P, ctx->dplan, w.Lam, ctx->status);
   TimingUser tu{sp, ev};
   int best = default_range(P);
@@ -875,7 +999,7 @@ vi_status run(vi_ctx* ctx, const std::vector<WinIn>& wins, const vi_opts* o, int
   if (!workspace) return fail(ctx, VI_EINVAL, "null workspace");
   if (((uintptr_t)workspace & 255) != 0) return fail(ctx, VI_EINVAL, "workspace must be 256-byte aligned");
   HIPCHK(ctx, hipSetDevice(ctx->device));
-  s = ensure_plan(ctx, wins, o->use_imu && o->bias_mode == VI_BIAS_GLOBAL);
+  s = ensure_plan(ctx, wins, o->use_imu != 0, o->use_imu && o->bias_mode == VI_BIAS_GLOBAL);
   if (s != VI_OK) return s;
   Plan& P = ctx->plan;
   size_t need = 0;
@@ -910,7 +1034,7 @@ vi_status run(vi_ctx* ctx, const std::vector<WinIn>& wins, const vi_opts* o, int
     std::vector<hipEvent_t> ev(kNumStages + 1);
     for (auto& e : ev) HIPCHK(ctx, hipEventCreate(&e));
     std::vector<double> acc(VI_NUM_STAGES, 0.0);
-    launch_reset_status(sp, ctx->status, P.n_win);
+    launch_reset_status(sp, ctx->status, P.n_win, w.seg_cnt, (int)P.segs.size());
     if (od.use_imu) launch_imu_info(sp, P, D, w.Lam, ctx->status);
     if (wa) launch_warm_prologue(sp, P, D, w, od, *wa, ww);
     TimingUser tu{sp, ev.data()};
@@ -963,7 +1087,7 @@ vi_status run(vi_ctx* ctx, const std::vector<WinIn>& wins, const vi_opts* o, int
       if (ctx->graph) { (void)hipGraphDestroy(ctx->graph); ctx->graph = nullptr; }
       ctx->have_graph = false;
       HIPCHK(ctx, hipStreamBeginCapture(sp, hipStreamCaptureModeThreadLocal));
-      launch_reset_status(sp, ctx->status, P.n_win);
+      launch_reset_status(sp, ctx->status, P.n_win, w.seg_cnt, (int)P.segs.size());
       if (od.use_imu) launch_imu_info(sp, P, D, w.Lam, ctx->status);
       if (wa) launch_warm_prologue(sp, P, D, w, od, *wa, ww);
       for (int it = 0; it < iters; ++it) launch_step(sp, P, D, w, od, it, ctx->status);
@@ -1074,7 +1198,7 @@ vi_status run_pgba(vi_ctx* ctx, const vi_camera* cam, int32_t n_kf, double* pose
   if (((uintptr_t)workspace & 255) != 0) return fail(ctx, VI_EINVAL, "workspace must be 256-byte aligned");
   HIPCHK(ctx, hipSetDevice(ctx->device));
   std::vector<WinIn> wins{in};
-  s = ensure_plan(ctx, wins);
+  s = ensure_plan(ctx, wins, false, false);
   if (s != VI_OK) return s;
   Plan& P = ctx->plan;
   size_t need = 0;
@@ -1254,7 +1378,7 @@ size_t vi_workspace_size_batched(int32_t n_windows, const vi_window* windows, co
     wins.push_back(in);
   }
   Plan P;
-  if (build_plan(nullptr, wins, P) != VI_OK) return 0;
+  if (build_plan(nullptr, wins, P, opts->use_imu != 0, false) != VI_OK) return 0;
   set_range(P, default_range(P));
   size_t b = 0;
   do_carve(P, nullptr, &b);
@@ -1289,7 +1413,7 @@ size_t vi_pgba_workspace_size(const vi_camera* cam, int32_t n_kf, const vi_edges
     return 0;
   std::vector<WinIn> wins{in};
   Plan P;
-  if (build_plan(nullptr, wins, P) != VI_OK) return 0;
+  if (build_plan(nullptr, wins, P, opts->use_imu != 0, false) != VI_OK) return 0;
   set_range(P, default_range(P));
   size_t b = 0;
   do_carve(P, nullptr, &b);
@@ -1376,7 +1500,7 @@ vi_status warm_windows(vi_ctx* ctx, int32_t n_windows, const vi_window* windows,
       return fail(ctx, VI_EINVAL, "window %d: its %d x %d cell grid does not fit the %d x %d canvas", w,
                   (windows[w].cam.H + 3) / 4, (windows[w].cam.W + 3) / 4, hq, wq);
   }
-  s = ensure_plan(ctx, wins, o->use_imu && o->bias_mode == VI_BIAS_GLOBAL);
+  s = ensure_plan(ctx, wins, o->use_imu != 0, o->use_imu && o->bias_mode == VI_BIAS_GLOBAL);
   if (s != VI_OK) return s;
   return refresh_windows(ctx, wins, o->invdepth_f32 != 0);
 }
@@ -1394,7 +1518,7 @@ size_t vi_warm_start_workspace_size(int32_t n_windows, const vi_window* windows,
     wins.push_back(in);
   }
   Plan P;
-  if (build_plan(nullptr, wins, P) != VI_OK) return 0;
+  if (build_plan(nullptr, wins, P, opts->use_imu != 0, false) != VI_OK) return 0;
   set_range(P, default_range(P));
   int hq, wq;
   warm_canvas(wins, &hq, &wq);

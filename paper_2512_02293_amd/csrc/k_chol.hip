@@ -37,6 +37,7 @@
 #include <algorithm>
 
 #include "vi_internal.h"
+#include "vi_math.h"
 
 namespace vi {
 
@@ -97,17 +98,6 @@ __device__ __forceinline__ void acc_to_lds(const double4_t (&acc)[2][2], double*
     for (int bn = 0; bn < 2; ++bn)
 #pragma unroll
       for (int r = 0; r < 4; ++r) T[(16 * bm + (l >> 4) + 4 * r) * LD + 16 * bn + (l & 15)] = acc[bm][bn][r];
-}
-
-__device__ __forceinline__ double rsqrt_refined(double v) {
-  // hardware reciprocal square root (relative error about 2^-23), then one
-  // third-order step: with e = 1 - v y^2, v^-1/2 = y (1 - e)^-1/2 =
-  // y (1 + e/2 + 3 e^2/8 + 5 e^3/16 + ...); the dropped terms are below 2^-64
-  // relative.  Four dependent operations after the estimate, where two
-  // Newton steps take six (the pivot chain of the leaf factor runs through it).
-  const double y = __builtin_amdgcn_rsq(v);
-  const double e = __builtin_fma(-v, y * y, 1.0);
-  return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
 }
 
 // ---------------------------------------------------------------------------

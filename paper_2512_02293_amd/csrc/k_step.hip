@@ -170,6 +170,12 @@ __device__ __forceinline__ float reduce16(float (&v)[16], int lane) {
   return r + dpp_f<kDppQuadXor1>(r);
 }
 
+}  // namespace
+}  // namespace vi
+#include "k_cond.h"   // uses set_status and reduce16
+namespace vi {
+namespace {
+
 // Running sum of per-block partial sums.  FP64: plain.  FP32: Kahan-
 // compensated (s holds the sum, c the running compensation), so the error
 // does not grow with the number of blocks.
@@ -392,19 +398,28 @@ __device__ void imu_residual_jacobian(const double* pose, const double* vel, con
 
 // One inertial factor per 256-thread workgroup (runs as extra workgroups of the
 // vision-assembly launch): H = J^T Lambda J, g = -J^T Lambda r, r^T Lambda r.
-// LDS: J (450), T (450), Lambda (225), r (15).  f is the global factor index.
-__device__ void imu_factor_block(int f, const WinDev& W, const double* __restrict__ Lam, double* __restrict__ Hf,
+// LDS: J (450), T (450), Lambda (225), r (15) and copies of the factor and of
+// the two keyframes' states, so that the one lane that forms the residual and
+// the Jacobian waits for memory once.  f is the global factor index.
+constexpr int kImuLds = 450 + 450 + 225 + 15 + 154 + 14 + 6 + 12 + 3;
+__device__ __forceinline__ void imu_factor_block(int f, const WinDev& W, const double* __restrict__ Lam, double* __restrict__ Hf,
                                  double* __restrict__ gf, double* __restrict__ icost, double* sm) {
   double* J = sm;
   double* T = J + 450;
   double* Lm = T + 450;
   double* r = Lm + 225;
+  double* Pm = r + 15;                    // vi_preint
+  double* Sm = Pm + 154;                  // poses (14), velocities (6), biases (12), gravity (3)
   const int l = threadIdx.x;
   const int lf = f - W.f_base;
+  if (l < 154) Pm[l] = ((const double*)(W.imu + lf))[l];
+  if (l < 35)
+    Sm[l] = l < 14 ? W.pose[(size_t)lf * 7 + l]
+                   : (l < 20 ? W.vel[(size_t)lf * 3 + l - 14] : (l < 32 ? W.bias[(size_t)lf * 6 + l - 20] : W.g[l - 32]));
   for (int e = l; e < 450; e += (int)blockDim.x) J[e] = 0.0;
   for (int e = l; e < 225; e += (int)blockDim.x) Lm[e] = Lam[(size_t)f * 225 + e];
   __syncthreads();
-  if (l == 0) imu_residual_jacobian(W.pose, W.vel, W.bias, W.imu + lf, W.g, lf, r, J);
+  if (l == 0) imu_residual_jacobian(Sm, Sm + 14, Sm + 20, (const vi_preint*)Pm, Sm + 32, 0, r, J);
   __syncthreads();
   for (int e = l; e < 450; e += (int)blockDim.x) {
     const int a = e / 15, b = e % 15;
@@ -417,12 +432,12 @@ __device__ void imu_factor_block(int f, const WinDev& W, const double* __restric
     const int a = e / 30, c = e % 30;
     double v = 0.0;
     for (int m = 0; m < 15; ++m) v += T[a * 15 + m] * J[m * 30 + c];
-    Hf[(size_t)f * 900 + e] = v;
+    agent_store(Hf + (size_t)f * 900 + e, v);
   }
   if (l < 30) {
     double v = 0.0;
     for (int m = 0; m < 15; ++m) v += T[l * 15 + m] * r[m];
-    gf[(size_t)f * 30 + l] = -v;
+    agent_store(gf + (size_t)f * 30 + l, -v);
   }
   if (l == 0) {
     double c = 0.0;
@@ -607,18 +622,36 @@ __global__ void __launch_bounds__(kVisThreads) k_vis_gram(OptsDev o, DevPlan D, 
                                                           double* __restrict__ hpart, double* __restrict__ gpart,
                                                           double* __restrict__ vcost, double* __restrict__ Hf,
                                                           double* __restrict__ gf, double* __restrict__ icost,
+                                                          double* __restrict__ cond, int* __restrict__ seg_cnt,
                                                           DevStatus* __restrict__ st) {
   constexpr bool kF64 = sizeof(R) == 8;
   constexpr int LDC = vis_ldc<R>();
-  extern __shared__ double sm[];
+  // 16-byte aligned whatever the fixed LDS variables take: the 128-bit operand
+  // reads of the Gram ran 2.3 times slower from an offset of 8
+  extern __shared__ __align__(16) double sm[];
   __shared__ double red[2][kVisWaves];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: per-wave choices stay scalar
   if ((int)blockIdx.y < imu_rows) {
     const int f = (int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x;
     if (f < F && o.use_imu && !(st && st[D.win_of_f[f]].conv)) {   // frozen windows keep their blocks
-      const WinDev W = D.win[D.win_of_f[f]];
+      const WinDev& W = D.win[D.win_of_f[f]];
       imu_factor_block(f, W, Lam, Hf, gf, icost, sm);
+      // the workgroup that finishes the last factor of a segment eliminates
+      // its velocity and bias unknowns: nobody waits, and the counter is back
+      // at zero for the next launch
+      __shared__ int last;
+      const SegDev& S = D.segs[D.f_seg[f]];
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's blocks have arrived
+      __syncthreads();
+      if (tid == 0) {
+        int* cnt = seg_cnt + D.f_seg[f];
+        const int before = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = before == S.nf - 1;
+        if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      __syncthreads();
+      if (last) cond_segment(o, S, W, Hf, gf, cond, sm, st ? st + S.w : nullptr);
     }
     return;
   }
@@ -1049,11 +1082,17 @@ __global__ void __launch_bounds__(kLocalThreads) k_local(int N, int nkr_max, int
                                                          double* __restrict__ ZB, double* __restrict__ ZV,
                                                          const double* __restrict__ vcost,
                                                          const double* __restrict__ icost, int use_imu,
-                                                         double* __restrict__ trace, int slot, double tol,
-                                                         DevStatus* __restrict__ st) {
-  extern __shared__ double sm[];
-  if ((int)blockIdx.x >= N) {
-    const int w = blockIdx.x - N;
+                                                         double* __restrict__ trace, int slot, double tol, int ngram,
+                                                         double* __restrict__ cond, DevStatus* __restrict__ st) {
+  extern __shared__ __align__(16) double sm[];
+  // the Grams of the eliminated segments, one tile per wave
+  if ((int)blockIdx.x < ngram) {
+    cond_gram(D.segs[D.gram_map[2 * blockIdx.x]], cond, D.gram_map[2 * blockIdx.x + 1] + (int)(threadIdx.x >> 6));
+    return;
+  }
+  const int blk = (int)blockIdx.x - ngram;
+  if (blk >= N) {
+    const int w = blk - N;
     cost_reduce_block(D.win[w], w, ncost, range, vcost, icost, use_imu, trace, slot, sm);
     // tolerance stop: F at this linearisation point against the previous one
     // (written by this same thread); once the relative decrease is at most tol
@@ -1065,7 +1104,7 @@ __global__ void __launch_bounds__(kLocalThreads) k_local(int N, int nkr_max, int
     }
     return;
   }
-  const int src = blockIdx.x;
+  const int src = blk;
   const WinDev& Wsrc = D.win[D.win_of_kf[src]];
   const int nkr = Wsrc.nkr;
   const bool ext = Wsrc.ext != 0;     // camera-IMU extrinsic: general M_j (else its block structure is used)
@@ -1354,69 +1393,10 @@ __global__ void __launch_bounds__(kLocalThreads) k_local(int N, int nkr_max, int
 // (so the Cholesky forward pass produces L^-1 s in that row), and whose
 // padding is the identity.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ bool coord_active(const OptsDev& o, int a, int ra, int N) {
-  if (ra < 6) return a >= o.n_fixed;
-  if (!o.use_imu) return false;
-  if (ra >= 9 && o.bias_fixed) return false;
-  if (ra >= 9 && o.bias_global) return a == N - 1;   // the shared bias sits in the last keyframe's slot
-  return true;
-}
-
-// inertial part of the entry ((a, ra), (b, cb)) of B: the blocks of the
-// factors (a - 1, a) and (a, a + 1) of the window (Hw: [F][30][30])
-__device__ __forceinline__ double imu_hess(const double* Hw, int N, int a, int ra, int b, int cb) {
-  double v = 0.0;
-  if (a == b) {
-    if (a > 0) v += Hw[(size_t)(a - 1) * 900 + (15 + ra) * 30 + 15 + cb];
-    if (a < N - 1) v += Hw[(size_t)a * 900 + ra * 30 + cb];
-  } else if (b == a + 1) {
-    v += Hw[(size_t)a * 900 + ra * 30 + 15 + cb];
-  } else if (a == b + 1) {
-    v += Hw[(size_t)b * 900 + (15 + ra) * 30 + cb];
-  }
-  return v;
-}
-
-// inertial part of w_xi at (b, cb) (gw: [F][30])
-__device__ __forceinline__ double imu_grad(const double* gw, int N, int b, int cb) {
-  double v = 0.0;
-  if (b > 0) v += gw[(size_t)(b - 1) * 30 + 15 + cb];
-  if (b < N - 1) v += gw[(size_t)b * 30 + cb];
-  return v;
-}
-
-// The same entries with one bias for the window (Table 6 (f)): the bias
-// coordinates of every keyframe are the one unknown in the last keyframe's
-// slot, so the folded system G^T B G sums an entry over the keyframes whose
-// bias it touches (those of the inertial factors next to the other index)
-__device__ double imu_hess_folded(const double* Hw, int N, int a, int ra, int b, int cb, bool global) {
-  const bool ga = global && ra >= 9, gb = global && cb >= 9;
-  if (!ga && !gb) return imu_hess(Hw, N, a, ra, b, cb);
-  double v = 0.0;
-  if (ga && gb) {
-    for (int f = 0; f < N - 1; ++f) {
-      const double* H = Hw + (size_t)f * 900;
-      v += H[ra * 30 + cb] + H[ra * 30 + 15 + cb] + H[(15 + ra) * 30 + cb] + H[(15 + ra) * 30 + 15 + cb];
-    }
-  } else if (gb) {
-    for (int b2 = max(a - 1, 0); b2 <= min(a + 1, N - 1); ++b2) v += imu_hess(Hw, N, a, ra, b2, cb);
-  } else {
-    for (int a2 = max(b - 1, 0); a2 <= min(b + 1, N - 1); ++a2) v += imu_hess(Hw, N, a2, ra, b, cb);
-  }
-  return v;
-}
-
-__device__ double imu_grad_folded(const double* gw, int N, int b, int cb, bool global) {
-  if (!(global && cb >= 9)) return imu_grad(gw, N, b, cb);
-  double v = 0.0;
-  for (int b2 = 0; b2 < N; ++b2) v += imu_grad(gw, N, b2, cb);
-  return v;
-}
-
 __global__ void k_assemble(OptsDev o, DevPlan D, const double* __restrict__ Z, const double* __restrict__ ZB,
                            const double* __restrict__ ZV, const double* __restrict__ Hf,
-                           const double* __restrict__ gf, double* __restrict__ A, int* __restrict__ flags,
-                           int* __restrict__ sync, DevStatus* st) {
+                           const double* __restrict__ gf, const double* __restrict__ cond, double* __restrict__ A,
+                           int* __restrict__ flags, int* __restrict__ sync, DevStatus* st) {
   const int w = blockIdx.y;
   const WinDev& W = D.win[w];
   const int N = W.N, n = W.n, npad = W.npad;
@@ -1439,8 +1419,9 @@ __global__ void k_assemble(OptsDev o, DevPlan D, const double* __restrict__ Z, c
   const int* poff = D.pair_off + W.pair_base;
   double val = 0.0;
   if (r < n && c < n) {
-    // block positions -> keyframes (the window's order of the reduced system)
-    const int a = D.kf_at[W.kf_base + r / 15], ra = r % 15, b = D.kf_at[W.kf_base + c / 15], cb = c % 15;
+    // rows -> keyframes (the window's order of the reduced system)
+    const int mr = D.row_map[W.x_off + r], mc = D.row_map[W.x_off + c];
+    const int a = mr >> 8, ra = mr & 255, b = mc >> 8, cb = mc & 255;
     if (coord_active(o, a, ra, N) && coord_active(o, b, cb, N)) {
       double bd = 0.0;
       if (ra < 6 && cb < 6) {
@@ -1474,6 +1455,8 @@ __global__ void k_assemble(OptsDev o, DevPlan D, const double* __restrict__ Z, c
         if (r == c) bd += vi;
       }
       if (r == c) val += o.lambda * bd;
+      // minus what the eliminated velocity and bias unknowns take
+      if (o.use_imu) val -= seg_entry(D, W, cond, a, ra, b, cb, o.bias_global != 0);
     } else {
       val = (r == c) ? 1.0 : 0.0;
     }
@@ -1481,7 +1464,8 @@ __global__ void k_assemble(OptsDev o, DevPlan D, const double* __restrict__ Z, c
   } else if (r < npad) {
     val = (r == c) ? 1.0 : 0.0;
   } else if (r == npad && c < n) {
-    const int b = D.kf_at[W.kf_base + c / 15], cb = c % 15;
+    const int mc = D.row_map[W.x_off + c];
+    const int b = mc >> 8, cb = mc & 255;
     if (coord_active(o, b, cb, N)) {
       if (cb < 6) {
         const int p0 = poff[b * N + b], p1 = poff[b * N + b + 1];
@@ -1494,7 +1478,8 @@ __global__ void k_assemble(OptsDev o, DevPlan D, const double* __restrict__ Z, c
             if (it0 + u < p1) val += v[u];
         }
       }
-      if (o.use_imu) val += imu_grad_folded(gw, N, b, cb, o.bias_global != 0);
+      if (o.use_imu)
+        val += imu_grad_folded(gw, N, b, cb, o.bias_global != 0) - seg_rhs(D, W, cond, b, cb, o.bias_global != 0);
     }
     if (!isfinite(val)) set_status(st + w, VI_ENONFINITE, n + 15 * b + cb);
   }
@@ -1505,46 +1490,64 @@ __global__ void k_assemble(OptsDev o, DevPlan D, const double* __restrict__ Z, c
 // back-substitution (Eq. 4: dd = C^-1 (w_d - E^T dxi)) and retraction.  The
 // E^T dxi term is L_p . u with u_e = M_i,e dxi_i + M_j,e dxi_j (pose parts),
 // the local increment of each edge; L_p is recomputed from the weights and the
-// Jacobians (cheaper than storing it).  Workgroups with blockIdx.y >= N retract
-// the keyframe states of window blockIdx.y - N.  A window whose status holds
-// an error is left untouched.
+// Jacobians (cheaper than storing it).  The first nseg rows of workgroups solve
+// for and retract the eliminated velocities and biases of one segment each
+// (first, because their chain takes longest), the next N are the sources, and
+// the last retract the keyframe states of one window each.  A window whose
+// status holds an error is left untouched.
 // ---------------------------------------------------------------------------
 template <typename R>
-__global__ void __launch_bounds__(256) k_backsub_retract(OptsDev o, int N, DevPlan D, const double* __restrict__ Rw,
+__global__ void __launch_bounds__(256, 5) k_backsub_retract(OptsDev o, int N, DevPlan D, const double* __restrict__ Rw,
                                                          const double* __restrict__ rel,
                                                          const double* __restrict__ Cd,
                                                          const double* __restrict__ wd,
-                                                         const double* __restrict__ x, int ppt, DevStatus* st) {
+                                                         const double* __restrict__ x, int ppt, int nseg,
+                                                         const double* __restrict__ cond, DevStatus* st) {
+  extern __shared__ double seg_lds[];
   __shared__ double u[kMaxOutDegree * 6];
   __shared__ double rel_s[kMaxOutDegree * 12];
   __shared__ double xcam[(kMaxOutDegree + 1) * 6];
   const int tid = threadIdx.x;
-  if ((int)blockIdx.y >= N) {
-    const int w = blockIdx.y - N;
+  if ((int)blockIdx.y < nseg) {
+    if (blockIdx.x != 0) return;
+    const SegDev& S = D.segs[blockIdx.y];
+    const WinDev& W = D.win[S.w];
+    if (st[S.w].code == 0 && st[S.w].conv == 0) cond_backsub(o, D, S, W, cond, x + W.x_off, seg_lds);
+    return;
+  }
+  const int src = (int)blockIdx.y - nseg;
+  if (src >= N) {
+    const int w = src - N;
     if (blockIdx.x != 0 || st[w].code != 0 || st[w].conv != 0) return;
     const WinDev& W = D.win[w];
     const double* xw = x + W.x_off;
     // one bias for the window: its increment (the last keyframe's slot) moves every keyframe's
-    const double* dxb = o.bias_global ? xw + (size_t)D.kf_pos[W.kf_base + W.N - 1] * 15 : nullptr;
+    const double* dxb = o.bias_global ? xw + D.kf_off[W.kf_base + W.N - 1] + 9 : nullptr;
     for (int t = tid; t < W.N; t += 256) {
-      const double* dx = xw + (size_t)D.kf_pos[W.kf_base + t] * 15;
-      const double* db = dxb ? dxb + 9 : dx + 9;
+      const int off = D.kf_off[W.kf_base + t];
+      const double* dx = xw + off;
+      // a separator's velocity and bias are in the reduced system too
+      const bool kept = off + 6 < W.n && D.row_map[W.x_off + off + 6] == ((t << 8) | 6);
       double* q = W.pose + (size_t)t * 7;
       quat_retract(q + 3, dx);
-      for (int k = 0; k < 3; ++k) {
-        q[k] += dx[3 + k];
-        W.vel[(size_t)t * 3 + k] += dx[6 + k];
-      }
-      for (int k = 0; k < 6; ++k) W.bias[(size_t)t * 6 + k] += db[k];
+      for (int k = 0; k < 3; ++k) q[k] += dx[3 + k];
+      if (kept)
+        for (int k = 0; k < 3; ++k) W.vel[(size_t)t * 3 + k] += dx[6 + k];
+      const double* db = dxb ? dxb : dx + 9;
+      if (kept || dxb)
+        for (int k = 0; k < 6; ++k) W.bias[(size_t)t * 6 + k] += db[k];
       if (W.rep_dxi) {
-        for (int k = 0; k < 9; ++k) W.rep_dxi[(size_t)t * 15 + k] = dx[k];
-        for (int k = 0; k < 6; ++k) W.rep_dxi[(size_t)t * 15 + 9 + k] = db[k];
+        double* o15 = W.rep_dxi + (size_t)t * 15;
+        for (int k = 0; k < 6; ++k) o15[k] = dx[k];
+        if (kept || !o.use_imu)
+          for (int k = 6; k < 9; ++k) o15[k] = kept ? dx[k] : 0.0;
+        if (kept || dxb || !o.use_imu)
+          for (int k = 0; k < 6; ++k) o15[9 + k] = (kept || dxb) ? db[k] : 0.0;
       }
     }
     if (tid == 0) st[w].iters += 1;
     return;
   }
-  const int src = blockIdx.y;
   const int w = D.win_of_kf[src];
   const WinDev W = D.win[w];
   const int HW = W.HW;
@@ -1562,7 +1565,7 @@ __global__ void __launch_bounds__(256) k_backsub_retract(OptsDev o, int N, DevPl
       const int s = i / 6, c = i % 6;
       const int kf = s == 0 ? src : D.jj[D.src_edges[e0 + s - 1]];
       const double* Rc = Rw + (size_t)kf * 9;
-      const double* xb = xw + (size_t)D.kf_pos[kf] * 15;
+      const double* xb = xw + D.kf_off[kf];
       double v = 0.0;
       for (int m = 0; m < 6; ++m) v += K_at(Wg, Rc, c, m) * xb[m];
       xcam[i] = v;
@@ -1574,8 +1577,8 @@ __global__ void __launch_bounds__(256) k_backsub_retract(OptsDev o, int N, DevPl
     const int e = D.src_edges[e0 + s];
     const double* Rt = rel + (size_t)e * 12;
     const double* Rj = Rw + (size_t)D.jj[e] * 9;
-    const double* xi = W.ext ? xcam : xw + (size_t)D.kf_pos[src] * 15;
-    const double* xj = W.ext ? xcam + 6 * (s + 1) : xw + (size_t)D.kf_pos[D.jj[e]] * 15;
+    const double* xi = W.ext ? xcam : xw + D.kf_off[src];
+    const double* xj = W.ext ? xcam + 6 * (s + 1) : xw + D.kf_off[D.jj[e]];
     double v = 0.0;
     for (int m = 0; m < 6; ++m) v += Mi_at(Rt, Rj, c, m) * xi[m] + Mj_at(Rj, c, m) * xj[m];
     u[i] = v;
@@ -1624,8 +1627,9 @@ __global__ void __launch_bounds__(256) k_backsub_retract(OptsDev o, int N, DevPl
   }
 }
 
-__global__ void k_reset_status(DevStatus* st, int n) {
+__global__ void k_reset_status(DevStatus* st, int n, int* cnt, int ncnt) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < ncnt) cnt[i] = 0;
   if (i < n) { st[i].code = 0; st[i].detail = 0; st[i].iters = 0; st[i].conv = 0; }
 }
 
@@ -1909,18 +1913,18 @@ __global__ void __launch_bounds__(256) k_warm_state(DevPlan D, double* __restric
 
 // dynamic LDS of the fused assembly: relative transforms, two E-tile
 // buffers, the C / w_d partials and 1/C of two chunks; the inertial
-// workgroups need 1140 doubles
-static size_t vis_lds(int kmax, bool f64) {
+// workgroups need kImuLds doubles, the one that eliminates a segment more
+static size_t vis_lds(int kmax, bool f64, int cond_len) {
   const size_t T = vis_tiles_T(kmax);
   const size_t esz = f64 ? sizeof(double) : sizeof(float);
   const size_t ldc = f64 ? vis_ldc<double>() : vis_ldc<float>();
   const size_t vis = esz * ((size_t)kMaxOutDegree * 12 + 2 * 16 * T * ldc + 2 * kVisWaves * 64 + 2 * 64);
-  const size_t imu = sizeof(double) * (450 + 450 + 225 + 15);
-  return std::max(vis, imu);
+  const size_t imu = sizeof(double) * kImuLds;
+  return std::max({vis, imu, cond_len > 0 ? sizeof(double) * cond_lds_doubles(cond_len) : 0});
 }
 
 typedef void (*VisKernel)(OptsDev, DevPlan, int, int, int, int, int, const double*, double*, double*, double*,
-                          double*, double*, double*, double*, double*, double*, double*, DevStatus*);
+                          double*, double*, double*, double*, double*, double*, double*, double*, int*, DevStatus*);
 
 // the instantiation of the fused assembly for the largest out-degree of a batch:
 // edge slots per wave ceil(kmax / 8), Gram tiles per wave ceil(T (T + 1) / 16)
@@ -1938,21 +1942,21 @@ static size_t local_lds(int kmax) {
   return sizeof(double) * std::max<size_t>(nq * nq + 4 * 36 * k + 9 * k + 6 * k, 2 * kLocalThreads);
 }
 
-void launch_reset_status(hipStream_t s, DevStatus* st, int n) {
-  hipLaunchKernelGGL(k_reset_status, dim3((n + 63) / 64), dim3(64), 0, s, st, n);
+void launch_reset_status(hipStream_t s, DevStatus* st, int n, int32_t* cnt, int ncnt) {
+  hipLaunchKernelGGL(k_reset_status, dim3((std::max(n, ncnt) + 63) / 64), dim3(64), 0, s, st, n, cnt, ncnt);
 }
 
 void chol_set_attributes();
 
-void step_set_attributes(int kmax) {
+void step_set_attributes(int kmax, int cond_len) {
   chol_set_attributes();
   // every instantiation of the fused assembly may run for some batch: each
   // gets the LDS cap of the largest out-degree it serves
   for (int km = 1; km <= kMaxOutDegree; ++km) {
     (void)hipFuncSetAttribute((const void*)vis_kernel<double>(km), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)vis_lds(kMaxOutDegree, true));
+                              (int)vis_lds(kMaxOutDegree, true, cond_len));
     (void)hipFuncSetAttribute((const void*)vis_kernel<float>(km), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)vis_lds(kMaxOutDegree, false));
+                              (int)vis_lds(kMaxOutDegree, false, cond_len));
   }
   (void)hipFuncSetAttribute((const void*)k_local, hipFuncAttributeMaxDynamicSharedMemorySize, (int)local_lds(kmax));
 }
@@ -1968,13 +1972,14 @@ static void launch_front(hipStream_t s, const Plan& P, const DevPlan& D, const W
   const int ncost = cost_slots(P);
   const bool f64 = o.precision != VI_PREC_MIXED;
   VisKernel kern = f64 ? vis_kernel<double>(P.kmax) : vis_kernel<float>(P.kmax);
-  hipLaunchKernelGGL(kern, dim3(nkr_run, N + imu_rows), dim3(kVisThreads), vis_lds(P.kmax, f64), s, o, D, imu_rows, F,
-                     P.nkr_max, ncost, P.range, w.Lam, w.Rw, w.rel, w.Cd, w.wd, w.hpart, w.gpart, w.vcost, w.Hf,
-                     w.gf, w.icost, st);
+  hipLaunchKernelGGL(kern, dim3(nkr_run, N + imu_rows), dim3(kVisThreads), vis_lds(P.kmax, f64, F > 0 ? P.cond_len : 0),
+                     s, o, D, imu_rows, F, P.nkr_max, ncost, P.range, w.Lam, w.Rw, w.rel, w.Cd, w.wd, w.hpart, w.gpart,
+                     w.vcost, w.Hf, w.gf, w.icost, w.cond, w.seg_cnt, st);
   done(kStVis);
-  hipLaunchKernelGGL(k_local, dim3(N + P.n_win), dim3(kLocalThreads), local_lds(P.kmax), s, N, P.nkr_max, ncost,
-                     P.range, D, w.Rw, w.rel, w.hpart, w.gpart, w.Z, w.ZB, w.ZV, w.vcost, w.icost, o.use_imu, w.trace,
-                     iter, o.tol, st);
+  const int ngram = P.segs.empty() ? 0 : (int)P.gram_map.size() / 2;
+  hipLaunchKernelGGL(k_local, dim3(ngram + N + P.n_win), dim3(kLocalThreads), local_lds(P.kmax), s, N, P.nkr_max,
+                     ncost, P.range, D, w.Rw, w.rel, w.hpart, w.gpart, w.Z, w.ZB, w.ZV, w.vcost, w.icost, o.use_imu,
+                     w.trace, iter, o.tol, ngram, w.cond, st);
   done(kStLocal);
 }
 
@@ -1983,9 +1988,9 @@ void launch_vis_assembly(hipStream_t s, const Plan& P, const DevPlan& D, const W
   const int nkr_run = (P.hw_max + P.range - 1) / P.range;
   const bool f64 = o.precision != VI_PREC_MIXED;
   VisKernel kern = f64 ? vis_kernel<double>(P.kmax) : vis_kernel<float>(P.kmax);
-  hipLaunchKernelGGL(kern, dim3(nkr_run, P.N), dim3(kVisThreads), vis_lds(P.kmax, f64), s, o, D, 0, 0, P.nkr_max,
+  hipLaunchKernelGGL(kern, dim3(nkr_run, P.N), dim3(kVisThreads), vis_lds(P.kmax, f64, 0), s, o, D, 0, 0, P.nkr_max,
                      cost_slots(P), P.range, w.Lam, w.Rw, w.rel, w.Cd, w.wd, w.hpart, w.gpart, w.vcost, w.Hf, w.gf,
-                     w.icost, st);
+                     w.icost, w.cond, w.seg_cnt, st);
 }
 
 void launch_vis_cost(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, const OptsDev& o) {
@@ -2007,7 +2012,7 @@ void launch_step(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, 
   size_t total_max = 0;
   for (const WinDev& W : P.win) total_max = std::max(total_max, (size_t)(W.npad + kCholNB) * W.npad);
   hipLaunchKernelGGL(k_assemble, dim3((unsigned)((total_max + 255) / 256), P.n_win), dim3(256), 0, s, o, D, w.Z,
-                     w.ZB, w.ZV, w.Hf, w.gf, w.A, w.flags, w.sync, st);
+                     w.ZB, w.ZV, w.Hf, w.gf, w.cond, w.A, w.flags, w.sync, st);
   done(kStAssemble);
   launch_chol(s, P, D, w, st);
   done(kStChol);
@@ -2017,8 +2022,9 @@ void launch_step(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, 
   // dependent loads, is then shared by more pixels)
   const int ppt = (int)std::min<long long>(4, std::max<long long>(1, P.pix_total / (256LL * 2048)));
   const int pxb = 256 * ppt;
-  hipLaunchKernelGGL(kbs, dim3((P.hw_max + pxb - 1) / pxb, N + P.n_win), dim3(256), 0, s, o, N, D, w.Rw,
-                     w.rel, w.Cd, w.wd, w.x, ppt, st);
+  const size_t seg_lds = P.cond_len > 0 ? sizeof(double) * (2 * kCondNV * P.cond_len + kCondCols) : 0;
+  hipLaunchKernelGGL(kbs, dim3((P.hw_max + pxb - 1) / pxb, N + P.n_win + (int)P.segs.size()), dim3(256), seg_lds, s, o,
+                     N, D, w.Rw, w.rel, w.Cd, w.wd, w.x, ppt, (int)P.segs.size(), w.cond, st);
   done(kStBacksub);
 }
 

@@ -29,6 +29,30 @@ constexpr int kMaxIters = 64;         // cost trace capacity of vi_ba_solve
 constexpr int kMaxKeyframes = 640;    // per window: the back-substitution keeps 2 x 15 N doubles in LDS
 constexpr int kTraceLen = 2 * (kMaxIters + 1);
 
+// Velocity / bias unknowns ("V", 9 per keyframe) are eliminated before the
+// reduced system is formed.  Only inertial factors touch them, so their block
+// of the normal equations is block tridiagonal along the keyframes.  The
+// keyframes are cut into segments by separator keyframes; the V of the
+// keyframes inside a segment are eliminated (k_cond.h), the V of the
+// separators stay in the reduced system beside their poses.
+//  * A segment couples all of its poses and its two chains run one keyframe
+//    after the other, so a window is cut about every kCondSpan keyframes (40 x
+//    56 maps, 4 iterations, the whole window as one segment -> cut: 28
+//    keyframes 785 -> 619 us with 6 edges per source and 890 -> 815 with 15; 16:
+//    541 -> 515).  Shorter spans keep more unknowns: about every 6 instead of
+//    every 12, 128 keyframes take 2156 instead of 2055 us; every 24, 48 take 937
+//    instead of 865.
+//  * A separator that fits the padding of the last tile of the reduced system
+//    costs nothing there and halves a chain, so more are taken while segments
+//    keep kCondMinLen keyframes (12 keyframes: 513 -> 465 us; at 6, segments of
+//    3 and 2 keyframes, 443 -> 449).
+constexpr int kCondSpan = 12;
+constexpr int kCondMinLen = 3;
+constexpr int kCondNV = 9;
+// status details of at least this hold keyframe * 15 + unknown of the window
+// (a pivot of the eliminated unknowns), not a coordinate of the reduced system
+constexpr int kNaturalDetail = 1 << 24;
+
 // Device status word of one window: first error (vi_status), its detail (e.g.
 // pivot index), and the number of committed steps.
 struct DevStatus {
@@ -50,6 +74,7 @@ struct WinDev {
   int pair_base;                     // offset of this window's pair table
   int flag_off, nflags;              // Cholesky tile flags [(nblk + 1) * nblk]
   int band;                          // tiles (i, j) with i - j > band are zero in S and in L
+  int seg_base, nseg;                // segments of eliminated velocity / bias unknowns
   int fc_off;                        // offset of the tile envelope (nblk + 1 entries) in chol_fc
   long long pix_base;                // global offset of the first keyframe's first pixel
   long long A_off, Linv_off, x_off;  // reduced system, diagonal-tile inverses, solution
@@ -70,6 +95,22 @@ struct WinDev {
   int rel_base, n_rel;               // global index of the window's first relative-pose factor
 };
 
+// One segment of eliminated velocity / bias unknowns: the V of keyframes a..b
+// (window indices).  Its columns are the unknowns of the reduced system that
+// they couple with: the poses of keyframes k0..k1 (the segment and its
+// neighbours), the V of the separators a - 1 and b + 1 where there are any
+// (columns vl.., vr..), with one global bias also its 6 unknowns (columns gb..,
+// inside vr.. where the last keyframe is the right neighbour), and last (nc)
+// the right-hand side.
+struct SegDev {
+  int32_t w, a, b, k0, k1, nc, ld;   // ld: columns rounded up to the 16 x 16 tiles of its Gram
+  int32_t vl, vr, gb;                // first column of each, -1: none
+  int32_t nf;                        // inertial factors that touch it
+  int32_t pad;
+  int64_t y_off, l_off, g_off;       // Y (9 per keyframe x ld), factors (162 per keyframe), Gram (ld x ld)
+};
+constexpr int kSegGramTiles = 16;    // Gram tiles per workgroup (one per wave)
+
 // Host-built description of one batch.
 struct Plan {
   int n_win = 0;
@@ -88,9 +129,16 @@ struct Plan {
   std::vector<int32_t> gram_off, z_off, zb_off;
   std::vector<int32_t> pair_off, pair_z, pair_zb;
   std::vector<int32_t> chol_tiles;             // ticket -> (window, (i << 16) | j)
-  // keyframe order of each window's reduced system: keyframe a (local) has
-  // its unknowns at block position kf_pos[kf_base + a]; kf_at is the inverse
-  std::vector<int32_t> kf_pos, kf_at;
+  // order of each window's reduced system: keyframe a (window index) has its
+  // unknowns from row kf_off[kf_base + a] on (6 pose unknowns, all 15 for a
+  // separator, 7 in the pose graph); row_map[x_off + r] = (a << 8) | unknown of
+  // row r, -1 in the padding
+  std::vector<int32_t> kf_off, row_map;
+  std::vector<SegDev> segs;
+  std::vector<int32_t> kf_seg;                 // [2 N] segments whose columns hold the keyframe's pose (-1: none)
+  std::vector<int32_t> f_seg;                  // [F] segment that eliminates with the factor
+  std::vector<int32_t> gram_map;               // (segment, first Gram tile) per workgroup of the segments' Grams
+  int cond_len = 0;                            // keyframes of the longest segment
   // per window, first nonzero tile column of every tile row of S and L (the
   // right-hand-side row last, 0): tiles (i, j < fc[i]) are zero in both
   std::vector<int32_t> chol_fc;
@@ -103,6 +151,8 @@ struct Plan {
   size_t flags_size = 0;
   size_t gram_size = 0, z_size = 0, zb_size = 0;
   size_t A_size = 0, Linv_size = 0, x_size = 0;
+  size_t cond_size = 0;                        // doubles of Y, factors and Grams of all segments
+  size_t seg_cap = 0;                          // arrival counters of the segments
 };
 
 // Device pointers into the plan upload.
@@ -112,7 +162,9 @@ struct DevPlan {
   const int32_t *pair_off, *pair_z, *pair_zb;
   const int32_t* chol_tiles;
   const int32_t *rel_ii, *rel_jj, *rel_z, *rel_zb;
-  const int32_t *kf_pos, *kf_at, *chol_fc;
+  const int32_t *kf_off, *row_map, *chol_fc;
+  const int32_t *kf_seg, *f_seg, *gram_map;
+  const SegDev* segs;
   const WinDev* win;
 };
 
@@ -139,6 +191,8 @@ struct Work {
   double* x;         // per window [npad]
   double* trace;     // [n_win][kTraceLen]  cost, n_valid per slot
   double* rcost;     // [R]  relative-pose factor costs (pose-graph adjustment)
+  double* cond;      // eliminated unknowns: Y, factors and Gram of every segment
+  int32_t* seg_cnt;  // [segments] inertial factors linearised so far (zero between launches)
 };
 
 struct OptsDev {
@@ -176,7 +230,8 @@ void launch_step(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, 
 // the first two stages only (autotuning of the assembly tiling)
 void launch_tune_stages(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, const OptsDev& o,
                         StageMark mark, void* mark_user);
-void launch_reset_status(hipStream_t s, DevStatus* st, int n);
+// also clears the arrival counters of the segments (cnt, ncnt)
+void launch_reset_status(hipStream_t s, DevStatus* st, int n, int32_t* cnt = nullptr, int ncnt = 0);
 // dd / db (optional): warm-start corrections (cells [n][HQ][WQ], [n][6]) applied
 // to the state first, so that the cost is that of the corrected state
 void launch_final_cost(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, const OptsDev& o,
@@ -199,7 +254,7 @@ void launch_pg_backsub(hipStream_t s, const Plan& P, const DevPlan& D, const Wor
                        DevStatus* st);
 void launch_pg_cost(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, int ncost, int range_px,
                     int slot, double tol, DevStatus* st);
-void step_set_attributes(int kmax);
+void step_set_attributes(int kmax, int cond_len);
 // warm start
 void wnet_set_attributes();
 // wprep (optional device scratch of wnet_prep_bytes()): the layers' weights are

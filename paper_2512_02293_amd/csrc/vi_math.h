@@ -7,6 +7,17 @@
 
 namespace vi {
 
+__device__ __forceinline__ double rsqrt_refined(double v) {
+  // hardware reciprocal square root (relative error about 2^-23), then one
+  // third-order step: with e = 1 - v y^2, v^-1/2 = y (1 - e)^-1/2 =
+  // y (1 + e/2 + 3 e^2/8 + 5 e^3/16 + ...); the dropped terms are below 2^-64
+  // relative.  Four dependent operations after the estimate, where two
+  // Newton steps take six (the pivot chain of the leaf factor runs through it).
+  const double y = __builtin_amdgcn_rsq(v);
+  const double e = __builtin_fma(-v, y * y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+}
+
 __device__ __forceinline__ void m3_mul(const double* A, const double* B, double* C) {
 #pragma unroll
   for (int r = 0; r < 3; ++r)
