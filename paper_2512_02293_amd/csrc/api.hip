@@ -430,7 +430,7 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
     const WinDev& W = P.win[P.win_of_kf[g]];
     // the fused assembly writes the tiles of (6 k + 1) columns for every
     // source, one tile (the right-hand-side column alone) when k = 0
-    const int T = (6 * k + 16) / 16;
+    const int T = vis_tiles_T(k, true);   // the larger of both
     P.gram_off[g] = (int32_t)go;
     P.z_off[g] = (int32_t)zo;
     P.zb_off[g] = (int32_t)zbo;
@@ -894,7 +894,7 @@ vi_status autotune_range(vi_ctx* ctx, const Work& w, const OptsDev& od) {
       if (pg) {
         // pose graph: the fused assembly of the loop pairs and the per-source blocks
         launch_vis_assembly(sp, P, ctx->dplan, w, od, ctx->status);
-        launch_pg_local(sp, P, ctx->dplan, w, ctx->status);
+        launch_pg_local(sp, P, ctx->dplan, w, od, ctx->status);
         HIPCHK(ctx, hipEventRecord(ev[kStLocal + 1], sp));
       } else {
         launch_tune_stages(sp, P, ctx->dplan, w, od, mark_event, &tu);
@@ -1223,7 +1223,7 @@ vi_status run_pgba(vi_ctx* ctx, const vi_camera* cam, int32_t n_kf, double* pose
   launch_reset_status(sp, ctx->status, P.n_win);
   for (int it = 0; it < iters; ++it) {
     launch_vis_assembly(sp, P, D, w, od, ctx->status);
-    launch_pg_local(sp, P, D, w, ctx->status);
+    launch_pg_local(sp, P, D, w, od, ctx->status);
     launch_pg_relpose(sp, P, D, w, ctx->status, true);
     launch_pg_cost(sp, P, D, w, ncost, P.range, it, od.tol, ctx->status);
     launch_pg_assemble(sp, P, D, w, od.n_fixed, od.lambda, ctx->status);

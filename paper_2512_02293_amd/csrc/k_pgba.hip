@@ -73,7 +73,7 @@ __device__ __forceinline__ double sum_part(const double* __restrict__ p, size_t 
 // ---------------------------------------------------------------------------
 constexpr int kPgThreads = 256;
 
-__global__ void __launch_bounds__(kPgThreads) k_local_pg(int nkr_max, DevPlan D, const double* __restrict__ Rw,
+__global__ void __launch_bounds__(kPgThreads) k_local_pg(int nkr_max, int wd_row, DevPlan D, const double* __restrict__ Rw,
                                                          const double* __restrict__ rel,
                                                          const double* __restrict__ hpart,
                                                          const double* __restrict__ gpart, double* __restrict__ Z,
@@ -98,7 +98,8 @@ __global__ void __launch_bounds__(kPgThreads) k_local_pg(int nkr_max, DevPlan D,
     return;
   }
   const int ncol = 6 * k, nq = ncol + 1;
-  const int T = (ncol + 16) / 16;
+  const int ngr = ncol + wd_row;                       // rows of the Gram
+  const int T = vis_tiles_T(k, wd_row);
   const int ntiles = T * (T + 1) / 2;
   double* Qs = sm;                  // [nq][nq] symmetric
   double* Hs = Qs + nq * nq;        // [k][36]
@@ -114,7 +115,7 @@ __global__ void __launch_bounds__(kPgThreads) k_local_pg(int nkr_max, DevPlan D,
     while ((I + 1) * (I + 2) / 2 <= t) ++I;
     const int J = t - I * (I + 1) / 2;
     const int a = 16 * I + (e >> 4), b = 16 * J + (e & 15);
-    if (a < nq && b < nq && a >= b) {
+    if (a < ngr && a >= b) {
       const double v = sum_part(gp + i, gstride, nkr);
       Qs[a * nq + b] = v;
       Qs[b * nq + a] = v;
@@ -134,7 +135,8 @@ __global__ void __launch_bounds__(kPgThreads) k_local_pg(int nkr_max, DevPlan D,
     pg_maps(rel + (size_t)e * 12, Rw + (size_t)D.jj[e] * 9, W.scale[ls] / W.scale[lj], Mi + 42 * s, Mj + 42 * s);
   }
   __syncthreads();
-  for (int i = tid; i < 6 * k; i += kPgThreads) gs[i] -= Qs[ncol * nq + i];
+  if (wd_row)   // (else it is in the gradient sums)
+    for (int i = tid; i < 6 * k; i += kPgThreads) gs[i] -= Qs[ncol * nq + i];
   auto X = [&](int s, int t, int m, int n) { return (s == t ? Hs[s * 36 + m * 6 + n] : 0.0) - Qs[(6 * s + m) * nq + 6 * t + n]; };
   // W_t[a][n] = sum_s sum_m M_i,s[m][a] X_st[m][n]
   for (int i = tid; i < 42 * k; i += kPgThreads) {
@@ -596,8 +598,9 @@ void pg_set_attributes() {
                             (int)pg_local_lds(kMaxOutDegree));
 }
 
-void launch_pg_local(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, DevStatus* st) {
-  hipLaunchKernelGGL(k_local_pg, dim3(P.N), dim3(kPgThreads), pg_local_lds(P.kmax), s, P.nkr_max, D, w.Rw, w.rel,
+void launch_pg_local(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, const OptsDev& o, DevStatus* st) {
+  hipLaunchKernelGGL(k_local_pg, dim3(P.N), dim3(kPgThreads), pg_local_lds(P.kmax), s, P.nkr_max,
+                     vis_wd_row(P, o), D, w.Rw, w.rel,
                      w.hpart, w.gpart, w.Z, w.ZB, w.ZV, st);
 }
 

@@ -202,7 +202,7 @@ struct BlockSum {
 // t_ji = R_j^T (p_i - p_j) / s_j.  i, j index the window's pose array.
 // inverse depth i of a window (FP64, or FP32 when the caller keeps FP32 maps)
 __device__ __forceinline__ double dep_load(const WinDev& W, size_t i) {
-  return W.invdepth32 ? (double)W.invdepth32[i] : W.invdepth[i];
+  return W.invdepth32 ? (double)as_global(W.invdepth32)[i] : as_global(W.invdepth)[i];
 }
 __device__ __forceinline__ void dep_store(const WinDev& W, size_t i, double v) {
   if (W.invdepth32)
@@ -316,7 +316,7 @@ __device__ __forceinline__ void pix_edge(const WinDev& W, const OptsDev& o, cons
 // inertial factors (Eq. 3): residual, 15x30 Jacobian (NULL J: residual only).
 // i is the index of the earlier keyframe in the window's arrays.
 // ---------------------------------------------------------------------------
-__device__ void imu_residual_jacobian(const double* pose, const double* vel, const double* bias,
+__device__ __forceinline__ void imu_residual_jacobian(const double* pose, const double* vel, const double* bias,
                                       const vi_preint* P, const double* g, int i, double* r, double* J) {
   const int j = i + 1;
   double Ri[9], Rj[9];
@@ -487,9 +487,6 @@ constexpr int kVisBlockChunks = 8;             // chunks per FP32 block sum
 template <typename R>
 constexpr int vis_ldc() { return sizeof(R) == 4 ? 68 : 66; }
 
-// Gram tiles (lower triangle of T x T) and edge slots per wave for a source
-// with k outgoing edges
-__host__ __device__ constexpr int vis_tiles_T(int k) { return (6 * k + 16) / 16; }
 
 __device__ __forceinline__ void tile_ij(int t, int& I, int& J) {
   int i = 0;
@@ -564,9 +561,17 @@ __device__ __forceinline__ void vis_pair(const R* rt, R fx, R fy, R cx, R cy, R 
   const bool valid = inpx && d > (R)0 && Pz > zmin * d;
   const R iz = recip<R>(valid ? Pz : (R)1);
   const R xp = Px * iz, yp = Py * iz, dz = d * iz;
-  const R wx = valid ? (R)wgx : (R)0, wy = valid ? (R)wgy : (R)0;
-  const R rx = valid ? (R)tgx - (fx * xp + cx) : (R)0;
-  const R ry = valid ? (R)tgy - (fy * yp + cy) : (R)0;
+  const R wx = (R)(valid ? wgx : 0.f), wy = (R)(valid ? wgy : 0.f);
+  R rx, ry;
+  if constexpr (sizeof(R) == 8) {
+    // (masked ahead of the conversion, one select each; the residual of an
+    // invalid pair meets a zero weight)
+    rx = (double)(valid ? tgx : 0.f) - (fx * xp + cx);
+    ry = (double)(valid ? tgy : 0.f) - (fy * yp + cy);
+  } else {
+    rx = valid ? (R)tgx - (fx * xp + cx) : (R)0;
+    ry = valid ? (R)tgy - (fy * yp + cy) : (R)0;
+  }
   const R xy = xp * yp;
   const R ux[6] = {xy, -((R)1 + xp * xp), yp, -dz, (R)0, xp * dz};
   const R uy[6] = {(R)1 + yp * yp, -xy, -xp, (R)0, -dz, yp * dz};
@@ -613,25 +618,14 @@ __device__ __forceinline__ void vis_pair(const R* rt, R fx, R fy, R cx, R cy, R 
   }
 }
 
-// SLOTS: edge slots per wave (k <= 8 SLOTS); TS: Gram tiles per wave (T (T + 1) / 2 <= 8 TS).
-template <typename R, int SLOTS, int TS>
-__global__ void __launch_bounds__(kVisThreads) k_vis_gram(OptsDev o, DevPlan D, int imu_rows, int F, int nkr_max,
-                                                          int ncost, int range, const double* __restrict__ Lam,
-                                                          double* __restrict__ Rw, double* __restrict__ rel,
-                                                          double* __restrict__ Cd, double* __restrict__ wd,
-                                                          double* __restrict__ hpart, double* __restrict__ gpart,
-                                                          double* __restrict__ vcost, double* __restrict__ Hf,
-                                                          double* __restrict__ gf, double* __restrict__ icost,
-                                                          double* __restrict__ cond, int* __restrict__ seg_cnt,
-                                                          DevStatus* __restrict__ st) {
-  constexpr bool kF64 = sizeof(R) == 8;
-  constexpr int LDC = vis_ldc<R>();
-  // 16-byte aligned whatever the fixed LDS variables take: the 128-bit operand
-  // reads of the Gram ran 2.3 times slower from an offset of 8
-  extern __shared__ __align__(16) double sm[];
-  __shared__ double red[2][kVisWaves];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: per-wave choices stay scalar
+// What both assembly kernels do ahead of their chunks: the workgroups of the
+// inertial rows linearise a factor (and eliminate a segment), a source without
+// edges writes its empty cost slot; true when the workgroup has nothing more
+// to do.
+__device__ __forceinline__ bool vis_other_work(const OptsDev& o, const DevPlan& D, int imu_rows, int F, int ncost,
+                                               int range, const double* Lam, double* vcost, double* Hf, double* gf,
+                                               double* icost, double* cond, int* seg_cnt, DevStatus* st, double* sm) {
+  const int tid = threadIdx.x;
   if ((int)blockIdx.y < imu_rows) {
     const int f = (int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x;
     if (f < F && o.use_imu && !(st && st[D.win_of_f[f]].conv)) {   // frozen windows keep their blocks
@@ -653,26 +647,38 @@ __global__ void __launch_bounds__(kVisThreads) k_vis_gram(OptsDev o, DevPlan D, 
       __syncthreads();
       if (last) cond_segment(o, S, W, Hf, gf, cond, sm, st ? st + S.w : nullptr);
     }
-    return;
+    return true;
   }
   const int src = blockIdx.y - imu_rows, kr = blockIdx.x;
-  if (st && st[D.win_of_kf[src]].conv) return;      // frozen by the tolerance stop: its state is unchanged
-  const WinDev W = D.win[D.win_of_kf[src]];
-  const int HW = W.HW;
-  const int p_beg = kr * range;
-  if (p_beg >= HW) return;
-  const int p_end = min(HW, p_beg + range);
-  const int ls = src - W.kf_base;
-  const int e0 = D.src_off[src];
-  const int k = D.src_off[src + 1] - e0;
-  const int ncol = 6 * k;
-  const int T = vis_tiles_T(k);
-  const int ntiles = T * (T + 1) / 2;
-  const int tsz = 16 * T * LDC;                   // one E-tile buffer
-  R* rel_s = (R*)sm;                              // [kMaxOutDegree][12]
-  R* Et = rel_s + kMaxOutDegree * 12;             // [2][16 T][LDC]
-  R* part = Et + 2 * tsz;                         // [2][kVisWaves][64]  C and w_d partials
-  R* invcd = part + 2 * kVisWaves * 64;           // [2][64]
+  if (st && st[D.win_of_kf[src]].conv) return true;      // frozen by the tolerance stop: its state is unchanged
+  const WinDev& W = D.win[D.win_of_kf[src]];
+  const int HW = W.HW, p_beg = kr * range;
+  if (p_beg >= HW) return true;
+  if (D.src_off[src + 1] == D.src_off[src]) {
+    // a keyframe without outgoing edges has no residuals (its C, w_d, Gram and
+    // blocks are never read): only the camera rotation, the non-finite
+    // inverse-depth check and an empty cost slot
+    const int ls = src - W.kf_base;
+    bool bad = false;
+    for (int p = p_beg + tid; p < min(HW, p_beg + range); p += kVisThreads)
+      bad = bad || !isfinite(dep_load(W, (size_t)ls * HW + p));
+    if (st && bad) set_status(st + D.win_of_kf[src], VI_ENONFINITE, -1);
+    if (tid == 0) {
+      const size_t b = ((size_t)src * ncost + kr) * 2;
+      vcost[b] = 0.0;
+      vcost[b + 1] = 0.0;
+    }
+  }
+  return false;
+}
+
+// relative transforms of the source's edges into LDS; the first range also
+// writes them and the camera rotation R_c of the keyframe to memory (R_c / s
+// with keyframe scales: R^T / s maps world offsets into the scaled camera frame)
+template <typename R>
+__device__ __forceinline__ void vis_transforms(const DevPlan& D, const WinDev& W, int src, int kr, int e0, int k,
+                                               R* rel_s, double* __restrict__ Rw, double* __restrict__ rel) {
+  const int tid = threadIdx.x, ls = src - W.kf_base;
   if (tid < k) {
     const int e = D.src_edges[e0 + tid];
     double r12[12];
@@ -682,28 +688,325 @@ __global__ void __launch_bounds__(kVisThreads) k_vis_gram(OptsDev o, DevPlan D, 
     if (kr == 0)
       for (int q = 0; q < 12; ++q) rel[(size_t)e * 12 + q] = r12[q];
   }
-  if (kr == 0 && tid == 0) {
-    // camera rotation R_c of the keyframe (R_c / s with keyframe scales:
-    // R^T / s maps world offsets into the scaled camera frame)
+  if (kr == 0 && tid == kVisThreads - 1) {
     double Rm[9], pc[3];
     cam_pose(W, ls, Rm, pc);
     const double is = W.scale ? 1.0 / W.scale[ls] : 1.0;
     for (int q = 0; q < 9; ++q) Rw[(size_t)src * 9 + q] = is * Rm[q];
   }
-  if (k == 0) {
-    // a keyframe without outgoing edges has no residuals (its C, w_d, Gram and
-    // blocks are never read): only the non-finite inverse-depth check and an
-    // empty cost slot.  k is uniform over the workgroup.
-    bool bad = false;
-    for (int p = p_beg + tid; p < p_end; p += kVisThreads) bad = bad || !isfinite(dep_load(W, (size_t)ls * HW + p));
-    if (st && bad) set_status(st + D.win_of_kf[src], VI_ENONFINITE, -1);
-    if (tid == 0) {
-      const size_t b = ((size_t)src * ncost + kr) * 2;
-      vcost[b] = 0.0;
-      vcost[b + 1] = 0.0;
-    }
-    return;
+}
+
+// this workgroup's cost and valid-pixel count into its slot
+__device__ __forceinline__ void vis_store_cost(double cost, double nval, int src, int kr, int ncost,
+                                               double* __restrict__ vcost) {
+  __shared__ double red[2][kVisWaves];
+  const int tid = threadIdx.x;
+  cost = wave_sum(cost);
+  nval = wave_sum(nval);
+  if ((tid & 63) == 0) { red[0][tid >> 6] = cost; red[1][tid >> 6] = nval; }
+  __syncthreads();
+  if (tid == 0) {
+    double c = 0.0, nv = 0.0;
+#pragma unroll
+    for (int q = 0; q < kVisWaves; ++q) { c += red[0][q]; nv += red[1][q]; }
+    const size_t b = ((size_t)src * ncost + kr) * 2;
+    vcost[b] = c;
+    vcost[b + 1] = nv;
   }
+}
+
+// FP64, up to 8 edges per source: one edge per wave.
+//
+// An FP64 MFMA occupies its SIMD's vector unit, so nothing is gained from
+// matrix and vector work side by side: a chunk costs the sum of both (8 edges:
+// 6 tiles of 16 MFMAs of 64 clocks over 4 SIMDs, and 2 edges a SIMD of some 200
+// instructions of 4 clocks) plus whatever latency is left open.  Hence one
+// barrier a chunk (every wave sums the chunk's C and w_d for itself, and a wave
+// evaluates its edge on chunk c + 1 in the same interval in which it forms its
+// Gram units of chunk c); operands of the Gram are on their way from LDS while
+// the MFMAs before them run; the right-hand side E^T w_d / C goes into each
+// edge's gradient sums by the wave that owns the edge instead of being one more
+// Gram row (48 rows are 6 tiles, 49 are 10); a unit of the Gram is half the
+// pixels of a tile, which spreads 1, 3 or 6 tiles over the SIMDs, dealt from the
+// last wave, the edges from the first.  64 windows of 3 to 8 edges per source:
+// 1093 -> 881 us; with two edges per wave (9 to 16) this form loses what it
+// gains to registers (24 keyframes, 12 edges: 57 -> 60 us), so those stay with
+// the form below.
+constexpr int kVisOneEdge = kVisWaves;             // largest out-degree of a batch for it
+constexpr int kVisUnits = 2;                       // Gram units per wave: 12 half tiles over 8 waves
+
+__global__ void __launch_bounds__(kVisThreads) k_vis_gram64(OptsDev o, DevPlan D, int imu_rows, int F, int nkr_max,
+                                                            int ncost, int range, const double* __restrict__ Lam,
+                                                            double* __restrict__ Rw, double* __restrict__ rel,
+                                                            double* __restrict__ Cd, double* __restrict__ wd,
+                                                            double* __restrict__ hpart, double* __restrict__ gpart,
+                                                            double* __restrict__ vcost, double* __restrict__ Hf,
+                                                            double* __restrict__ gf, double* __restrict__ icost,
+                                                            double* __restrict__ cond, int* __restrict__ seg_cnt,
+                                                            DevStatus* __restrict__ st) {
+  constexpr int TU = kVisUnits;
+  constexpr int LDC = vis_ldc<double>();
+  // 16-byte aligned whatever the fixed LDS variables take: the 128-bit operand
+  // reads of the Gram ran 2.3 times slower from an offset of 8
+  extern __shared__ __align__(16) double sm[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: per-wave choices stay scalar
+  if (vis_other_work(o, D, imu_rows, F, ncost, range, Lam, vcost, Hf, gf, icost, cond, seg_cnt, st, sm)) return;
+  const int src = blockIdx.y - imu_rows, kr = blockIdx.x;
+  const WinDev& W = D.win[D.win_of_kf[src]];
+  const int HW = W.HW, WW = W.W;
+  const int p_beg = kr * range, p_end = min(HW, p_beg + range);
+  const int ls = src - W.kf_base;
+  const int e0 = D.src_off[src];
+  const int k = D.src_off[src + 1] - e0;
+  const int T = vis_tiles_T(k, false);
+  const int ntiles = T * (T + 1) / 2;
+  const int tsz = 16 * T * LDC;                    // one E-tile buffer
+  double* rel_s = sm;                              // [kMaxOutDegree][12]
+  double* Et = rel_s + kMaxOutDegree * 12;         // [2][16 T][LDC]
+  double* part = Et + 2 * tsz;                     // [2][2][kVisWaves][64]  C and w_d partials of two chunks
+  double* invs = part + 4 * kVisWaves * 64;        // [kVisWaves][64]  1/C, each wave its own
+  vis_transforms(D, W, src, kr, e0, k, rel_s, Rw, rel);
+  if (k == 0) return;
+  for (int i = tid; i < 2 * tsz + 4 * kVisWaves * 64; i += kVisThreads) Et[i] = 0.0;
+  __syncthreads();
+
+  const size_t dsrc = (size_t)ls * HW;             // this keyframe's inverse depths start here
+  double* Cds = Cd + W.pix_base + dsrc;
+  double* wds = wd + W.pix_base + dsrc;
+  const double fx = W.fx, fy = W.fy, cx = W.cx, cy = W.cy, zmin = o.z_min, eta = o.eta;
+  const double ifx = 1.0 / fx, ify = 1.0 / fy;
+  EdgeAcc<double> acc;
+  acc.zero();
+  double4_t gacc[TU];
+#pragma unroll
+  for (int u = 0; u < TU; ++u) gacc[u] = double4_t{0.0, 0.0, 0.0, 0.0};
+  double cost = 0.0, nval = 0.0;
+  bool bad = false;
+  // targets, weights and inverse depth of a chunk are loaded one chunk ahead;
+  // their addresses are uniform up to the lane (lanes past the range repeat its
+  // last pixel)
+  const auto tgt = as_global(W.target), wgt = as_global(W.weight);
+  const bool mine = wave < k;                      // this wave owns an edge
+  const long long eoff = mine ? (long long)(D.src_edges[e0 + wave] - W.e_base) * 2 * HW : 0;
+  const auto dep = as_global(W.invdepth) + dsrc;    // (FP32 depths come with mixed precision only)
+  float ntx = 0.f, nty = 0.f, nwx = 0.f, nwy = 0.f;
+  double nd = 0.0;
+  auto prefetch = [&](int c) {
+    const unsigned pl = (unsigned)min(lane, p_end - 1 - c) & 63u;
+    nd = (dep + c)[pl];
+    if (mine) {
+      const auto tx = tgt + (eoff + c), ty = tx + HW, wx = wgt + (eoff + c), wy = wx + HW;
+      ntx = tx[pl];
+      nty = ty[pl];
+      nwx = wx[pl];
+      nwy = wy[pl];
+    }
+  };
+  // this lane's pixel (column x, row y) of the chunk that is evaluated next
+  int xq = (p_beg + lane) % WW, yq = (p_beg + lane) / WW;
+  auto edge = [&](int c, int buf) {
+    const bool inpx = c + lane < p_end;
+    const double qx = ((double)xq - cx) * ifx, qy = ((double)yq - cy) * ify;
+    xq += 64;
+    while (xq >= WW) { xq -= WW; ++yq; }
+    bad = bad || (inpx && !isfinite(nd));
+    if (mine) {
+      double Cp = 0.0, Wp = 0.0;
+      vis_pair<double, LDC>(rel_s + wave * 12, fx, fy, cx, cy, zmin, qx, qy, nd, inpx, ntx, nty, nwx, nwy, acc,
+                            Et + buf * tsz + 6 * wave * LDC + lane, Cp, Wp, cost, nval);
+      double* pt = part + (buf * 2 * kVisWaves + wave) * 64 + lane;
+      pt[0] = Cp;
+      pt[kVisWaves * 64] = Wp;
+    }
+    if (c + 64 < p_end) prefetch(c + 64);
+  };
+  // Gram units of this wave: unit q = 7 - wave + 8 u is half q % 2 of tile q / 2;
+  // oA, oB: its operands' offsets in an E buffer
+  const int g4 = lane >> 4, m16 = lane & 15;
+  const int q0 = kVisWaves - 1 - wave;
+  const int nu = (2 * ntiles - q0 + kVisWaves - 1) / kVisWaves;       // at most TU
+  const int h = 8 * (q0 & 1);
+  int oA[TU], oB[TU];
+#pragma unroll
+  for (int u = 0; u < TU; ++u) {
+    int I = 0, J = 0;
+    if (u < nu) tile_ij((q0 + kVisWaves * u) / 2, I, J);
+    oA[u] = 16 * LDC * I;
+    oB[u] = 16 * LDC * J;
+  }
+  // lane (g4, m16) supplies pixels 16 g4 + h .. + 7 of a tile, 4 k-steps at a
+  // time: the next 4 are on their way from LDS while the MFMAs of these run
+  auto gram = [&](int buf) {
+    if (nu <= 0) return;
+    const double* E = Et + buf * tsz + m16 * LDC + 16 * g4 + h;
+    double2_t v[4], na[2], nb[2];
+    auto load = [&](int off_a, int off_b) {
+      const double2_t* pa = (const double2_t*)(E + off_a);
+      const double2_t* pb = (const double2_t*)(E + off_b);
+      na[0] = pa[0];
+      nb[0] = pb[0];
+      na[1] = pa[1];
+      nb[1] = pb[1];
+    };
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = ((const double2_t*)(invs + 64 * wave + 16 * g4 + h))[q];
+    load(oA[0], oB[0]);
+#pragma unroll
+    for (int u = 0; u < TU; ++u) {
+      if (u < nu) {
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+          double ab[8];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            ab[q] = na[q >> 1][q & 1];
+            ab[4 + q] = nb[q >> 1][q & 1] * v[2 * hh + (q >> 1)][q & 1];
+          }
+          pin8(ab);
+          if (hh == 0) load(oA[u] + 4, oB[u] + 4);
+          else if (u + 1 < TU) load(oA[min(u + 1, TU - 1)], oB[min(u + 1, TU - 1)]);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) gacc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(ab[q], ab[4 + q], gacc[u], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+  };
+  // C and w_d of the chunk at c0 from the partials of the waves that own edges,
+  // and this wave's share of the right-hand side
+  auto sums = [&](int c0, int buf) {
+    const double* pt = part + buf * 2 * kVisWaves * 64 + lane;
+    constexpr int kHalf = kVisWaves / 2;
+    double C = eta, Wv = 0.0, own[6];
+    // everything is loaded before the first sum: one LDS latency, not four
+    const double* E = Et + buf * tsz + 6 * min(wave, k - 1) * LDC + lane;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) own[q] = E[q * LDC];
+    double pc[kHalf], pw[kHalf];
+#pragma unroll
+    for (int q = 0; q < kHalf; ++q) { pc[q] = pt[q * 64]; pw[q] = pt[(kVisWaves + q) * 64]; }
+    if (k > kHalf) {
+      double hc[kHalf], hw[kHalf];
+#pragma unroll
+      for (int q = 0; q < kHalf; ++q) { hc[q] = pt[(kHalf + q) * 64]; hw[q] = pt[(kVisWaves + kHalf + q) * 64]; }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < kHalf; ++q) { C += pc[q]; Wv += pw[q]; }
+#pragma unroll
+      for (int q = 0; q < kHalf; ++q) { C += hc[q]; Wv += hw[q]; }
+    } else {
+#pragma unroll
+      for (int q = 0; q < kHalf; ++q) { C += pc[q]; Wv += pw[q]; }
+    }
+    const bool inpx = c0 + lane < p_end;
+    const double inv = (inpx && C > 0.0) ? recip<double>(C) : 0.0;
+    invs[64 * wave + lane] = inv;
+    if (wave == kVisWaves - 1 && inpx) {
+      Cds[c0 + lane] = C;
+      wds[c0 + lane] = Wv;
+    }
+    const double wi = Wv * inv;
+    if (mine)
+#pragma unroll
+      for (int q = 0; q < 6; ++q) acc.g[q] -= own[q] * wi;
+    wave_lds_sync();
+  };
+  prefetch(p_beg);
+  edge(p_beg, 0);
+  int c0 = p_beg, buf = 0;
+  for (; c0 + 64 < p_end; c0 += 64, buf ^= 1) {
+    __syncthreads();
+    sums(c0, buf);
+    edge(c0 + 64, buf ^ 1);
+    gram(buf);
+  }
+  __syncthreads();
+  sums(c0, buf);
+  gram(buf);
+  // a non-finite inverse depth fails the window (the state is left as it is)
+  if (st && bad) set_status(st + D.win_of_kf[src], VI_ENONFINITE, -1);
+  // the second halves of the tiles join the first ones
+  const bool first = h == 0;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < TU; ++u)
+    if (u < nu && !first)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) Et[(q0 + kVisWaves * u) / 2 * 256 + r * 64 + lane] = gacc[u][r];
+  __syncthreads();
+  double* out = gpart + D.gram_off[src] + (size_t)kr * ntiles * 256;
+#pragma unroll
+  for (int u = 0; u < TU; ++u) {
+    const int t = (q0 + kVisWaves * u) / 2;
+    if (u < nu && first)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        out[(size_t)t * 256 + (g4 + 4 * r) * 16 + m16] = gacc[u][r] + Et[t * 256 + r * 64 + lane];
+  }
+  // the edge's partials: lane l holds element l >> 2 of each 16-value half
+  if (mine) {
+    double v[16], w[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = acc.h[i];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) w[i] = acc.h[16 + i];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) w[5 + i] = acc.g[i];
+#pragma unroll
+    for (int i = 11; i < 16; ++i) w[i] = 0.0;
+    const double a = reduce16(v, lane), b = reduce16(w, lane);
+    double* hp = hpart + ((size_t)(e0 + wave) * nkr_max + kr) * 32;
+    const int el = lane >> 2;
+    if ((lane & 3) == 0) {
+      hp[el] = a;
+      if (el < 11) hp[16 + el] = b;
+    }
+  }
+  vis_store_cost(cost, nval, src, kr, ncost, vcost);
+}
+
+// Mixed precision, and FP64 from 9 edges per source on: two barriers a chunk,
+// the last wave forms C and w_d between them; w_d is the last row of the Gram.
+// SLOTS: edge slots per wave (k <= 8 SLOTS); TS: Gram tiles per wave (T (T + 1) / 2
+// <= 8 TS).
+template <typename R, int SLOTS, int TS>
+__global__ void __launch_bounds__(kVisThreads) k_vis_gram(OptsDev o, DevPlan D, int imu_rows, int F, int nkr_max,
+                                                          int ncost, int range, const double* __restrict__ Lam,
+                                                          double* __restrict__ Rw, double* __restrict__ rel,
+                                                          double* __restrict__ Cd, double* __restrict__ wd,
+                                                          double* __restrict__ hpart, double* __restrict__ gpart,
+                                                          double* __restrict__ vcost, double* __restrict__ Hf,
+                                                          double* __restrict__ gf, double* __restrict__ icost,
+                                                          double* __restrict__ cond, int* __restrict__ seg_cnt,
+                                                          DevStatus* __restrict__ st) {
+  constexpr bool kF64 = sizeof(R) == 8;
+  constexpr int LDC = vis_ldc<R>();
+  // 16-byte aligned whatever the fixed LDS variables take: the 128-bit operand
+  // reads of the Gram ran 2.3 times slower from an offset of 8
+  extern __shared__ __align__(16) double sm[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: per-wave choices stay scalar
+  if (vis_other_work(o, D, imu_rows, F, ncost, range, Lam, vcost, Hf, gf, icost, cond, seg_cnt, st, sm)) return;
+  const int src = blockIdx.y - imu_rows, kr = blockIdx.x;
+  const WinDev W = D.win[D.win_of_kf[src]];
+  const int HW = W.HW;
+  const int p_beg = kr * range;
+  const int p_end = min(HW, p_beg + range);
+  const int ls = src - W.kf_base;
+  const int e0 = D.src_off[src];
+  const int k = D.src_off[src + 1] - e0;
+  const int ncol = 6 * k;
+  const int T = vis_tiles_T(k, true);
+  const int ntiles = T * (T + 1) / 2;
+  const int tsz = 16 * T * LDC;                   // one E-tile buffer
+  R* rel_s = (R*)sm;                              // [kMaxOutDegree][12]
+  R* Et = rel_s + kMaxOutDegree * 12;             // [2][16 T][LDC]
+  R* part = Et + 2 * tsz;                         // [2][kVisWaves][64]  C and w_d partials
+  R* invcd = part + 2 * kVisWaves * 64;           // [2][64]
+  vis_transforms(D, W, src, kr, e0, k, rel_s, Rw, rel);
+  if (k == 0) return;
   for (int i = tid; i < 2 * tsz; i += kVisThreads) Et[i] = (R)0;
   __syncthreads();
 
@@ -741,10 +1044,10 @@ __global__ void __launch_bounds__(kVisThreads) k_vis_gram(OptsDev o, DevPlan D, 
     for (int u = 0; u < SLOTS; ++u) {
       if (wave + kVisWaves * u < k) {
         const size_t t = eoff[u] + pp;
-        ntx[u] = W.target[t];
-        nty[u] = W.target[t + HW];
-        nwx[u] = W.weight[t];
-        nwy[u] = W.weight[t + HW];
+        ntx[u] = as_global(W.target)[t];
+        nty[u] = as_global(W.target)[t + HW];
+        nwx[u] = as_global(W.weight)[t];
+        nwy[u] = as_global(W.weight)[t + HW];
       }
     }
   };
@@ -935,18 +1238,7 @@ __global__ void __launch_bounds__(kVisThreads) k_vis_gram(OptsDev o, DevPlan D, 
       if (el < 11) hp[16 + el] = hs_b[u].value();
     }
   }
-  cost = wave_sum(cost);
-  nval = wave_sum(nval);
-  if (lane == 0) { red[0][wave] = cost; red[1][wave] = nval; }
-  __syncthreads();
-  if (tid == 0) {
-    double c = 0.0, nv = 0.0;
-#pragma unroll
-    for (int q = 0; q < kVisWaves; ++q) { c += red[0][q]; nv += red[1][q]; }
-    const size_t b = ((size_t)src * ncost + kr) * 2;
-    vcost[b] = c;
-    vcost[b + 1] = nv;
-  }
+  vis_store_cost(cost, nval, src, kr, ncost, vcost);
 }
 
 // ---------------------------------------------------------------------------
@@ -1083,7 +1375,7 @@ __global__ void __launch_bounds__(kLocalThreads) k_local(int N, int nkr_max, int
                                                          const double* __restrict__ vcost,
                                                          const double* __restrict__ icost, int use_imu,
                                                          double* __restrict__ trace, int slot, double tol, int ngram,
-                                                         double* __restrict__ cond, DevStatus* __restrict__ st) {
+                                                         int wd_row, double* __restrict__ cond, DevStatus* __restrict__ st) {
   extern __shared__ __align__(16) double sm[];
   // the Grams of the eliminated segments, one tile per wave
   if ((int)blockIdx.x < ngram) {
@@ -1122,7 +1414,8 @@ __global__ void __launch_bounds__(kLocalThreads) k_local(int N, int nkr_max, int
     return;
   }
   const int ncol = 6 * k, nq = ncol + 1;
-  const int T = (ncol + 16) / 16;
+  const int ngr = ncol + wd_row;                       // rows of the Gram
+  const int T = vis_tiles_T(k, wd_row);
   const int ntiles = T * (T + 1) / 2;
   double* Qs = sm;                  // [nq][nq] symmetric
   double* Mi = Qs + nq * nq;        // [k][36]  M_i of edge s (with the extrinsic: M_i K_i)
@@ -1181,7 +1474,7 @@ __global__ void __launch_bounds__(kLocalThreads) k_local(int N, int nkr_max, int
       while ((I + 1) * (I + 2) / 2 <= t) ++I;
       const int J = t - I * (I + 1) / 2;
       const int a = 16 * I + (e >> 4), b = 16 * J + (e & 15);
-      if (a < nq && b < nq && a >= b) {
+      if (a < ngr && a >= b) {
         Qs[a * nq + b] = vq[h];
         Qs[b * nq + a] = vq[h];
       }
@@ -1209,7 +1502,8 @@ __global__ void __launch_bounds__(kLocalThreads) k_local(int N, int nkr_max, int
     }
   }
   __syncthreads();
-  for (int i = tid; i < k * 6; i += NT) gs[i] -= Qs[ncol * nq + i];
+  if (wd_row)   // (else it is in the gradient sums)
+    for (int i = tid; i < k * 6; i += NT) gs[i] -= Qs[ncol * nq + i];
   // W_t = sum_s M_i,s^T X_st,  X_st = delta_st H_s - Q_st
   for (int i = tid; i < k * 36; i += NT) {
     const int t = i / 36, a = (i % 36) / 6, b = i % 6;
@@ -1914,11 +2208,16 @@ __global__ void __launch_bounds__(256) k_warm_state(DevPlan D, double* __restric
 // dynamic LDS of the fused assembly: relative transforms, two E-tile
 // buffers, the C / w_d partials and 1/C of two chunks; the inertial
 // workgroups need kImuLds doubles, the one that eliminates a segment more
+static bool vis_one_edge(int kmax, bool f64) { return f64 && kmax <= kVisOneEdge; }
+
 static size_t vis_lds(int kmax, bool f64, int cond_len) {
-  const size_t T = vis_tiles_T(kmax);
+  const bool one = vis_one_edge(kmax, f64);
+  const size_t T = vis_tiles_T(kmax, !one);
   const size_t esz = f64 ? sizeof(double) : sizeof(float);
   const size_t ldc = f64 ? vis_ldc<double>() : vis_ldc<float>();
-  const size_t vis = esz * ((size_t)kMaxOutDegree * 12 + 2 * 16 * T * ldc + 2 * kVisWaves * 64 + 2 * 64);
+  // (one: the partials of two chunks and 1/C of one, each wave its own)
+  const size_t vis = esz * ((size_t)kMaxOutDegree * 12 + 2 * 16 * T * ldc +
+                            (one ? 5 * kVisWaves * 64 : 2 * kVisWaves * 64 + 2 * 64));
   const size_t imu = sizeof(double) * kImuLds;
   return std::max({vis, imu, cond_len > 0 ? sizeof(double) * cond_lds_doubles(cond_len) : 0});
 }
@@ -1926,17 +2225,26 @@ static size_t vis_lds(int kmax, bool f64, int cond_len) {
 typedef void (*VisKernel)(OptsDev, DevPlan, int, int, int, int, int, const double*, double*, double*, double*,
                           double*, double*, double*, double*, double*, double*, double*, double*, int*, DevStatus*);
 
-// the instantiation of the fused assembly for the largest out-degree of a batch:
-// edge slots per wave ceil(kmax / 8), Gram tiles per wave ceil(T (T + 1) / 16)
+// the fused assembly for the largest out-degree of a batch: k_vis_gram64, or the
+// instantiation with edge slots per wave ceil(kmax / 8) and Gram tiles per wave
+// ceil(T (T + 1) / 16)
 template <typename R>
-static VisKernel vis_kernel(int kmax) {
-  const int T = vis_tiles_T(kmax);
+static VisKernel vis_gram_kernel(int kmax) {
+  const int T = vis_tiles_T(kmax, true);
   const int ts = (T * (T + 1) / 2 + kVisWaves - 1) / kVisWaves;
   const int slots = (kmax + kVisWaves - 1) / kVisWaves;
-  if (slots <= 1) return ts <= 1 ? k_vis_gram<R, 1, 1> : k_vis_gram<R, 1, 2>;
-  if (slots == 2) return ts <= 2 ? k_vis_gram<R, 2, 2> : (ts == 3 ? k_vis_gram<R, 2, 3> : k_vis_gram<R, 2, 4>);
+  if constexpr (sizeof(R) == 4)
+    if (slots <= 1) return ts <= 1 ? k_vis_gram<R, 1, 1> : k_vis_gram<R, 1, 2>;
+  if (slots <= 2) return ts <= 2 ? k_vis_gram<R, 2, 2> : (ts == 3 ? k_vis_gram<R, 2, 3> : k_vis_gram<R, 2, 4>);
   return k_vis_gram<R, 3, 4>;
 }
+static VisKernel vis_kernel(int kmax, bool f64) {
+  if (vis_one_edge(kmax, f64)) return k_vis_gram64;
+  return f64 ? vis_gram_kernel<double>(kmax) : vis_gram_kernel<float>(kmax);
+}
+// whether the Gram holds w_d as its last row
+int vis_wd_row(const Plan& P, const OptsDev& o) { return vis_one_edge(P.kmax, o.precision != VI_PREC_MIXED) ? 0 : 1; }
+
 static size_t local_lds(int kmax) {
   const size_t k = kmax, nq = 6 * k + 1;
   return sizeof(double) * std::max<size_t>(nq * nq + 4 * 36 * k + 9 * k + 6 * k, 2 * kLocalThreads);
@@ -1953,9 +2261,9 @@ void step_set_attributes(int kmax, int cond_len) {
   // every instantiation of the fused assembly may run for some batch: each
   // gets the LDS cap of the largest out-degree it serves
   for (int km = 1; km <= kMaxOutDegree; ++km) {
-    (void)hipFuncSetAttribute((const void*)vis_kernel<double>(km), hipFuncAttributeMaxDynamicSharedMemorySize,
+    (void)hipFuncSetAttribute((const void*)vis_kernel(km, true), hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)vis_lds(kMaxOutDegree, true, cond_len));
-    (void)hipFuncSetAttribute((const void*)vis_kernel<float>(km), hipFuncAttributeMaxDynamicSharedMemorySize,
+    (void)hipFuncSetAttribute((const void*)vis_kernel(km, false), hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)vis_lds(kMaxOutDegree, false, cond_len));
   }
   (void)hipFuncSetAttribute((const void*)k_local, hipFuncAttributeMaxDynamicSharedMemorySize, (int)local_lds(kmax));
@@ -1971,7 +2279,7 @@ static void launch_front(hipStream_t s, const Plan& P, const DevPlan& D, const W
   const int imu_rows = (F + nkr_run - 1) / nkr_run;
   const int ncost = cost_slots(P);
   const bool f64 = o.precision != VI_PREC_MIXED;
-  VisKernel kern = f64 ? vis_kernel<double>(P.kmax) : vis_kernel<float>(P.kmax);
+  VisKernel kern = vis_kernel(P.kmax, f64);
   hipLaunchKernelGGL(kern, dim3(nkr_run, N + imu_rows), dim3(kVisThreads), vis_lds(P.kmax, f64, F > 0 ? P.cond_len : 0),
                      s, o, D, imu_rows, F, P.nkr_max, ncost, P.range, w.Lam, w.Rw, w.rel, w.Cd, w.wd, w.hpart, w.gpart,
                      w.vcost, w.Hf, w.gf, w.icost, w.cond, w.seg_cnt, st);
@@ -1979,7 +2287,7 @@ static void launch_front(hipStream_t s, const Plan& P, const DevPlan& D, const W
   const int ngram = P.segs.empty() ? 0 : (int)P.gram_map.size() / 2;
   hipLaunchKernelGGL(k_local, dim3(ngram + N + P.n_win), dim3(kLocalThreads), local_lds(P.kmax), s, N, P.nkr_max,
                      ncost, P.range, D, w.Rw, w.rel, w.hpart, w.gpart, w.Z, w.ZB, w.ZV, w.vcost, w.icost, o.use_imu,
-                     w.trace, iter, o.tol, ngram, w.cond, st);
+                     w.trace, iter, o.tol, ngram, vis_wd_row(P, o), w.cond, st);
   done(kStLocal);
 }
 
@@ -1987,7 +2295,7 @@ void launch_vis_assembly(hipStream_t s, const Plan& P, const DevPlan& D, const W
                          DevStatus* st) {
   const int nkr_run = (P.hw_max + P.range - 1) / P.range;
   const bool f64 = o.precision != VI_PREC_MIXED;
-  VisKernel kern = f64 ? vis_kernel<double>(P.kmax) : vis_kernel<float>(P.kmax);
+  VisKernel kern = vis_kernel(P.kmax, f64);
   hipLaunchKernelGGL(kern, dim3(nkr_run, P.N), dim3(kVisThreads), vis_lds(P.kmax, f64, 0), s, o, D, 0, 0, P.nkr_max,
                      cost_slots(P), P.range, w.Lam, w.Rw, w.rel, w.Cd, w.wd, w.hpart, w.gpart, w.vcost, w.Hf, w.gf,
                      w.icost, w.cond, w.seg_cnt, st);

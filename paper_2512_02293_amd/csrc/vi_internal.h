@@ -109,6 +109,9 @@ struct SegDev {
   int32_t pad;
   int64_t y_off, l_off, g_off;       // Y (9 per keyframe x ld), factors (162 per keyframe), Gram (ld x ld)
 };
+// 16 x 16 tiles along a side of the Gram of a source with k outgoing edges:
+// 6 k rows, or with w_d one more
+constexpr int vis_tiles_T(int k, bool wd_row) { return (6 * k + (wd_row ? 16 : 15)) / 16; }
 constexpr int kSegGramTiles = 16;    // Gram tiles per workgroup (one per wave)
 
 // Host-built description of one batch.
@@ -246,7 +249,8 @@ void launch_vis_cost(hipStream_t s, const Plan& P, const DevPlan& D, const Work&
 // pose-graph adjustment in Sim(3) (k_pgba.hip)
 size_t pg_local_lds(int kmax);
 void pg_set_attributes();
-void launch_pg_local(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, DevStatus* st);
+int vis_wd_row(const Plan& P, const OptsDev& o);
+void launch_pg_local(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, const OptsDev& o, DevStatus* st);
 void launch_pg_relpose(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, DevStatus* st, bool jac);
 void launch_pg_assemble(hipStream_t s, const Plan& P, const DevPlan& D, const Work& w, int n_fixed, double lambda,
                         DevStatus* st);

@@ -18,6 +18,14 @@ __device__ __forceinline__ double rsqrt_refined(double v) {
   return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
 }
 
+// A pointer that was itself loaded from memory, declared as one to global
+// memory: through the generic type its loads are flat ones, which count as LDS
+// operations too, so that every wait for LDS waits for them.
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) T* as_global(T* p) {
+  return (__attribute__((address_space(1))) T*)p;
+}
+
 __device__ __forceinline__ void m3_mul(const double* A, const double* B, double* C) {
 #pragma unroll
   for (int r = 0; r < 3; ++r)
