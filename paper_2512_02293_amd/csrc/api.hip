@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <numeric>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -243,13 +244,81 @@ std::vector<int> rcm_order(int N, const std::vector<std::vector<int>>& adj) {
   return order;
 }
 
-// first nonzero scalar column of each scalar row of S (lower triangle), the
-// dim[a] unknowns of keyframe a starting at row off[a]
+// Nested dissection of a sequence of keyframes along its order: the first part
+// L, the rest R without the keyframes T next to L, and T; L and R (from its far
+// end towards T) are independent of each other, so the factorisation runs
+// through both at once, and T comes last.  levels > 1: L and R again.  Appends
+// to out, -1 where the next keyframe has to start a tile of its own (with a
+// tile shared between two parts the second would wait for the first).
+constexpr int kCutLevels = 2;                            // at most 4 independent parts
+constexpr int kCutPad = ((1 << kCutLevels) - 1) * (kCholNB - 1);   // rows that they may skip
+
+void dissect(const std::vector<int>& seq, int levels, const std::vector<int>& dim,
+             const std::vector<std::vector<int>>& adj, std::vector<char>& mark, std::vector<int>& out) {
+  const int n = (int)seq.size();
+  int cut = -1, best = 0;
+  for (int a : seq) best += dim[a];
+  const int all = best;
+  if (levels > 0) {
+    // cuts at every 32nd of the sequence: the longest chain L or R, then T
+    for (int q = 4; q <= 28; ++q) {
+      const int m = (int)((long long)n * q / 32);
+      if (m < 1) continue;
+      int l = 0, t = 0;
+      for (int p = 0; p < m; ++p) l += dim[seq[p]];
+      for (int p = 0; p < m; ++p)
+        for (int u : adj[seq[p]]) mark[u] = 1;
+      for (int p = m; p < n; ++p)
+        if (mark[seq[p]]) t += dim[seq[p]];
+      for (int p = 0; p < m; ++p)
+        for (int u : adj[seq[p]]) mark[u] = 0;
+      const int chain = std::max(l, all - l - t) + t + kCholNB;
+      if (chain < best && all - l - t > 0) {
+        best = chain;
+        cut = m;
+      }
+    }
+  }
+  if (cut < 0) {
+    if (!out.empty()) out.push_back(-1);
+    out.insert(out.end(), seq.begin(), seq.end());
+    return;
+  }
+  std::vector<int> L(seq.begin(), seq.begin() + cut), R, T;
+  for (int a : L)
+    for (int u : adj[a]) mark[u] = 1;
+  for (int p = cut; p < n; ++p) (mark[seq[p]] ? T : R).push_back(seq[p]);
+  for (int a : L)
+    for (int u : adj[a]) mark[u] = 0;
+  std::reverse(R.begin(), R.end());
+  dissect(L, levels - 1, dim, adj, mark, out);
+  dissect(R, levels - 1, dim, adj, mark, out);
+  out.insert(out.end(), T.begin(), T.end());
+}
+
+// row at which each keyframe of a sequence starts (see dissect for -1); the
+// number of rows
+int sequence_rows(const std::vector<int>& seq, const std::vector<int>& dim, std::vector<int>& off) {
+  off.assign(dim.size(), 0);
+  int r = 0;
+  for (int a : seq) {
+    if (a < 0) {
+      r = (r + kCholNB - 1) / kCholNB * kCholNB;
+    } else {
+      off[a] = r;
+      r += dim[a];
+    }
+  }
+  return r;
+}
+
+// first nonzero scalar column of each of the n scalar rows of S (lower
+// triangle), the dim[a] unknowns of keyframe a starting at row off[a]; rows of
+// no keyframe are those of the identity
 void scalar_envelope(const std::vector<int>& dim, const std::vector<Coupling>& cpl, const std::vector<int>& off,
-                     std::vector<int>& fcs) {
-  int n = 0;
-  for (int d : dim) n += d;
-  fcs.assign(n, 0);
+                     int n, std::vector<int>& fcs) {
+  fcs.resize(n);
+  for (int r = 0; r < n; ++r) fcs[r] = r;
   for (size_t a = 0; a < dim.size(); ++a)
     for (int r = 0; r < dim[a]; ++r) fcs[off[a] + r] = off[a];
   for (const Coupling& c : cpl) {
@@ -322,6 +391,8 @@ struct Envelope {
   std::vector<int> fc;
   long long work = 0;
   int band = 0;
+  int chain = 0;             // longest chain of block columns that wait for one another
+  std::vector<int> depth;    // position of each block column in its chain
 };
 
 Envelope tile_envelope(const std::vector<int>& fcs, int n, int nblk) {
@@ -340,8 +411,19 @@ Envelope tile_envelope(const std::vector<int>& fcs, int n, int nblk) {
   for (int i = 0; i <= nblk; ++i)
     for (int j = E.fc[i]; j <= std::min(i, nblk - 1); ++j) E.work += 1 + (j - std::max(E.fc[i], E.fc[j]));
   E.band = std::min(nblk - 1, (wsc + kCholNB - 1) / kCholNB);
+  E.depth.assign(nblk, 1);
+  for (int j = 0; j < nblk; ++j) {
+    for (int k = E.fc[j]; k < j; ++k) E.depth[j] = std::max(E.depth[j], E.depth[k] + 1);
+    E.chain = std::max(E.chain, E.depth[j]);
+  }
   return E;
 }
+
+// Relative time of the dataflow factorisation over an envelope: its block
+// columns take about 10 us each one after the other, beside which the tile
+// updates of a column (about 1 us on one of some 250 waves at a time) hardly
+// count.
+double dataflow_cost(const Envelope& E) { return E.chain + (double)E.work / 2500.0; }
 
 vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool use_imu, bool bias_global) {
   P = Plan();
@@ -463,6 +545,7 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
   // per window: reduced system and gather lists of its assembly.  Pose block
   // (a, b) <- Z blocks of every source whose touched set contains a and b.
   size_t A_off = 0, L_off = 0, x_off = 0;
+  std::vector<std::vector<int>> depth(nw);
   size_t A_cap[2] = {0, 0}, L_cap[2] = {0, 0}, x_cap[2] = {0, 0}, f_cap[2] = {0, 0}, c_cap[2] = {0, 0},
          s_cap[2] = {0, 0};
   for (int w = 0; w < nw; ++w) {
@@ -476,20 +559,6 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
       for (int a = 0; a < W.N; ++a)
         if (sep[a]) dim[a] = 15;
     }
-    W.n = 0;
-    for (int d : dim) W.n += d;
-    W.npad = (W.n + kCholNB - 1) / kCholNB * kCholNB;
-    W.nblk = W.npad / kCholNB;
-    W.A_off = (long long)A_off;
-    W.Linv_off = (long long)L_off;
-    W.x_off = (long long)x_off;
-    W.flag_off = (int)P.flags_size;
-    W.nflags = (W.nblk + 2) * W.nblk;   // tile flags, then the back-substitution's x_b flags
-    P.flags_size += (size_t)W.nflags;
-    A_off += (size_t)(W.npad + kCholNB) * W.npad;
-    L_off += (size_t)W.nblk * kCholNB * kCholNB;
-    x_off += (size_t)W.npad;
-    P.nblk_max = std::max(P.nblk_max, W.nblk);
     std::vector<std::vector<std::pair<int, int>>> items((size_t)W.N * W.N);
     for (int g = W.kf_base; g < W.kf_base + W.N; ++g) {
       const int k = cnt[g];
@@ -533,25 +602,69 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
       std::sort(v.begin(), v.end());
       v.erase(std::unique(v.begin(), v.end()), v.end());
     }
-    // natural order unless the reverse Cuthill-McKee order lowers the work of
-    // the factorisation path this window takes (tile updates of the dataflow
-    // path, the band of the one-workgroup path)
-    std::vector<int> off(W.N), fcs;
-    for (int a = 0, r = 0; a < W.N; r += dim[a++]) off[a] = r;
-    scalar_envelope(dim, cpl, off, fcs);
-    Envelope env = tile_envelope(fcs, W.n, W.nblk);
-    const bool small_path = W.npad <= kCholSmallMaxNpad;
+    // Natural order unless another one suits the factorisation path of this
+    // window better: the reverse Cuthill-McKee order, by the band on the
+    // one-workgroup path, and on the dataflow path by its cost, there also
+    // either of them dissected into 2 or 4 parts.  The keyframe with the shared
+    // bias couples with every other one: it stays out of the dissection and
+    // comes last.
+    int n0 = 0;
+    for (int d : dim) n0 += d;
+    std::vector<int> seq(W.N), off, fcs;
+    for (int a = 0; a < W.N; ++a) seq[a] = a;
+    Envelope env;
+    auto measure = [&](const std::vector<int>& q, std::vector<int>& o, Envelope& e) {
+      const int n = sequence_rows(q, dim, o);
+      scalar_envelope(dim, cpl, o, n, fcs);
+      e = tile_envelope(fcs, n, (n + kCholNB - 1) / kCholNB);
+      return n;
+    };
+    W.n = measure(seq, off, env);
+    const bool small_path = (n0 + kCholNB - 1) / kCholNB * kCholNB <= kCholSmallMaxNpad;
     if (env.band > 0) {
+      auto consider = [&](const std::vector<int>& q) {
+        std::vector<int> off2;
+        Envelope env2;
+        const int n2 = measure(q, off2, env2);
+        if (small_path ? env2.band < env.band : dataflow_cost(env2) < dataflow_cost(env)) {
+          W.n = n2;
+          off.swap(off2);
+          env = std::move(env2);
+        }
+      };
       const std::vector<int> rcm = rcm_order(W.N, adj);
-      std::vector<int> off2(W.N);
-      for (int q = 0, r = 0; q < W.N; r += dim[rcm[q++]]) off2[rcm[q]] = r;
-      scalar_envelope(dim, cpl, off2, fcs);
-      Envelope env2 = tile_envelope(fcs, W.n, W.nblk);
-      if (small_path ? env2.band < env.band : env2.work < env.work) {
-        off.swap(off2);
-        env = std::move(env2);
+      consider(rcm);
+      if (!small_path) {
+        const int hub = !pg && use_imu && bias_global ? W.N - 1 : -1;
+        std::vector<std::vector<int>> adj2 = adj;
+        if (hub >= 0) {
+          for (auto& v : adj2) v.erase(std::remove(v.begin(), v.end(), hub), v.end());
+          adj2[hub].clear();
+        }
+        std::vector<char> mark(W.N, 0);
+        for (std::vector<int> base : {seq, hub >= 0 ? rcm_order(W.N, adj2) : rcm}) {
+          base.erase(std::remove(base.begin(), base.end(), hub), base.end());
+          for (int levels = 1; levels <= kCutLevels; ++levels) {
+            std::vector<int> q;
+            dissect(base, levels, dim, adj2, mark, q);
+            if (hub >= 0) q.push_back(hub);
+            consider(q);
+          }
+        }
       }
     }
+    W.npad = (W.n + kCholNB - 1) / kCholNB * kCholNB;
+    W.nblk = W.npad / kCholNB;
+    W.A_off = (long long)A_off;
+    W.Linv_off = (long long)L_off;
+    W.x_off = (long long)x_off;
+    W.flag_off = (int)P.flags_size;
+    W.nflags = (W.nblk + 2) * W.nblk;   // tile flags, then the back-substitution's x_b flags
+    P.flags_size += (size_t)W.nflags;
+    A_off += (size_t)(W.npad + kCholNB) * W.npad;
+    L_off += (size_t)W.nblk * kCholNB * kCholNB;
+    x_off += (size_t)W.npad;
+    P.nblk_max = std::max(P.nblk_max, W.nblk);
     P.row_map.resize(x_off, -1);
     for (int a = 0; a < W.N; ++a) {
       P.kf_off[W.kf_base + a] = off[a];
@@ -584,7 +697,8 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
       // the reduced systems with and without eliminated unknowns
       for (int g = 0; g < 2; ++g) {
         const CondLayout C = cond_layout(W.N, g != 0);
-        const size_t np = (size_t)(C.n + kCholNB - 1) / kCholNB * kCholNB;
+        size_t np = (size_t)(C.n + kCholNB - 1) / kCholNB * kCholNB;
+        if (np > (size_t)kCholSmallMaxNpad) np = (size_t)(C.n + kCutPad + kCholNB - 1) / kCholNB * kCholNB;
         A_cap[g] += (np + kCholNB) * np;
         L_cap[g] += np * kCholNB;
         x_cap[g] += np;
@@ -595,8 +709,25 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
       P.cond_size += cond.doubles;
     }
     W.band = env.band;
+    depth[w] = env.depth;
     W.fc_off = (int)P.chol_fc.size();
     P.chol_fc.insert(P.chol_fc.end(), env.fc.begin(), env.fc.end());
+    // behind it the block columns in chain order, for each column the number of
+    // them up to its own position in its chain, and for each block row (with the
+    // right-hand side) the position of the first one it needs
+    std::vector<int32_t> ord(W.nblk), pos(W.nblk);
+    std::iota(ord.begin(), ord.end(), 0);
+    std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return env.depth[x] < env.depth[y]; });
+    for (int p = 0; p < W.nblk; ++p) pos[ord[p]] = p;
+    P.chol_fc.insert(P.chol_fc.end(), ord.begin(), ord.end());
+    for (int j = 0; j < W.nblk; ++j)
+      P.chol_fc.push_back((int32_t)(std::upper_bound(ord.begin(), ord.end(), env.depth[j],
+                                                     [&](int d, int k) { return d < env.depth[k]; }) - ord.begin()));
+    for (int i = 0; i <= W.nblk; ++i) {
+      int32_t beg = W.nblk;
+      for (int k = env.fc[i]; k < std::min(i, W.nblk); ++k) beg = std::min(beg, pos[k]);
+      P.chol_fc.push_back(beg);
+    }
     // this window's table: entries pair_base .. pair_base + N*N (the last one is its end)
     W.pair_base = (int)P.pair_off.size();
     for (size_t q = 0; q < items.size(); ++q) {
@@ -609,37 +740,56 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
     P.pair_off.push_back((int32_t)P.pair_z.size());
   }
   if (P.pair_z.empty()) { P.pair_z.push_back(0); P.pair_zb.push_back(0); }
-  // Cholesky tickets of the windows too large for the one-workgroup path:
-  // column j, then window, then block row i (nblk = the right-hand-side
-  // block), so that every tile depends on smaller tickets only
-  for (int j = 0; j < P.nblk_max; ++j)
-    for (int w = 0; w < nw; ++w) {
+  // Cholesky tickets of the windows too large for the one-workgroup path, by
+  // the position of column j in its chain, then window, column, block row i
+  // (nblk = the right-hand-side block), so that every tile depends on smaller
+  // tickets only and independent chains start together
+  std::vector<std::vector<std::pair<int, int>>> at;      // by position: (window, column)
+  for (int w = 0; w < nw; ++w) {
+    if (P.win[w].npad <= kCholSmallMaxNpad) continue;
+    for (int j = 0; j < P.win[w].nblk; ++j) {
+      const size_t d = (size_t)depth[w][j];
+      if (at.size() <= d) at.resize(d + 1);
+      at[d].push_back({w, j});
+    }
+  }
+  for (const auto& cols : at)
+    for (const auto& wj : cols) {
+      const int w = wj.first, j = wj.second;
       const WinDev& W = P.win[w];
-      if (j >= W.nblk || W.npad <= kCholSmallMaxNpad) continue;
       const int32_t* fc = &P.chol_fc[W.fc_off];
-      // the diagonal tile, unless the ticket of tile (j, j - 1) carries it;
-      // tile (j + 1, j) then carries the diagonal tile j + 1 (kPairTicket);
+      // the diagonal tile, unless the ticket of tile (j, j - 1) carries it: tile
+      // (j + 1, j) carries the diagonal tile j + 1 (kPairTicket) when column
+      // j + 1 follows on j in its chain (else a longer chain ends in it);
       // tiles outside the envelope are zero in S and in L
-      if (j == 0 || fc[j] > j - 1) {
+      auto paired = [&](int c) { return fc[c] < c && depth[w][c] == depth[w][c - 1] + 1; };
+      if (!paired(j)) {
         P.chol_tiles.push_back(w);
         P.chol_tiles.push_back((j << 16) | j);
       }
       for (int i = j + 1; i <= W.nblk; ++i) {
         if (fc[i] > j) continue;
         P.chol_tiles.push_back(w);
-        P.chol_tiles.push_back((i << 16) | j | ((i == j + 1 && i < W.nblk) ? kPairTicketFlag : 0));
+        P.chol_tiles.push_back((i << 16) | j | ((i == j + 1 && i < W.nblk && paired(i)) ? kPairTicketFlag : 0));
       }
     }
   P.n_tickets = (int)(P.chol_tiles.size() / 2);
   // then the back-substitution's block columns, last column first, two per
-  // ticket (c and c - 1; the ticket of block 0 alone when nblk is odd)
-  for (int c = P.nblk_max - 1; c >= 0; --c)
+  // ticket where both are of one chain (c and c - 1: kPairTicketFlag)
+  std::vector<int> next(nw);
+  for (int w = 0; w < nw; ++w) next[w] = P.win[w].npad <= kCholSmallMaxNpad ? -1 : P.win[w].nblk - 1;
+  for (bool more = true; more;) {
+    more = false;
     for (int w = 0; w < nw; ++w) {
-      const WinDev& W = P.win[w];
-      if (c >= W.nblk || W.npad <= kCholSmallMaxNpad || (W.nblk - 1 - c) % 2 != 0) continue;
+      const int c = next[w];
+      if (c < 0) continue;
+      const bool two = c > 0 && P.chol_fc[P.win[w].fc_off + c] < c;
       P.chol_tiles.push_back(w);
-      P.chol_tiles.push_back(c);
+      P.chol_tiles.push_back(c | (two ? kPairTicketFlag : 0));
+      next[w] = c - (two ? 2 : 1);
+      more = true;
     }
+  }
   P.n_bs = (int)(P.chol_tiles.size() / 2) - P.n_tickets;
   P.row_map.resize(x_off, -1);
   if (P.gram_map.empty()) P.gram_map.push_back(0);
@@ -658,7 +808,8 @@ int natural_coord(const Plan& P, int w, int c) {
   const WinDev& W = P.win[w];
   if (c >= kNaturalDetail) return c - kNaturalDetail;
   if (c < 0 || c >= W.n) return c;
-  const int32_t m = P.row_map[(size_t)W.x_off + c];
+  int32_t m = P.row_map[(size_t)W.x_off + c];
+  while (m < 0 && c > 0) m = P.row_map[(size_t)W.x_off + --c];   // a row between two parts: the one before it
   return (m >> 8) * P.pdim + (m & 255);
 }
 

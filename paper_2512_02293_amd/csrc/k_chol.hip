@@ -59,17 +59,31 @@ __device__ __forceinline__ int load_flag(const int* f) {
   return __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Wait (whole wave) until *f is set.  false: the batch was aborted.
-__device__ __forceinline__ bool wait_flag(const int* f, int* sync) {
+// Wait (whole wave) until *f is set, without a fence.  false: the batch was
+// aborted.  near: the wave is on the chain of diagonal factors or next to it;
+// the others poll less often, and the abort flag, one word that all waves
+// share, is read at every 32nd poll only (thousands of waves wait at a time,
+// and their polls slow the chain down: 24 us a block column with every wave
+// polling both flags each 128 clocks, 9 us with few of them waiting).
+__device__ __forceinline__ bool spin_flag(const int* f, int* sync, bool near) {
   int spins = 0;
   while (__builtin_amdgcn_readfirstlane(load_flag(f)) == 0) {
-    if (__builtin_amdgcn_readfirstlane(load_flag(sync + 1)) != 0) return false;
-    if (++spins > kSpinLimit) {
-      if (threadIdx.x == 0) __hip_atomic_store(sync + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return false;
+    if ((++spins & 31) == 0) {
+      if (__builtin_amdgcn_readfirstlane(load_flag(sync + 1)) != 0) return false;
+      if (spins > kSpinLimit) {
+        if (threadIdx.x == 0) __hip_atomic_store(sync + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return false;
+      }
     }
-    __builtin_amdgcn_s_sleep(2);
+    if (near) __builtin_amdgcn_s_sleep(1);
+    else __builtin_amdgcn_s_sleep(32);
   }
+  return true;
+}
+
+// the same with the acquire fence
+__device__ __forceinline__ bool wait_flag(const int* f, int* sync, bool near) {
+  if (!spin_flag(f, sync, near)) return false;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   return true;
 }
@@ -83,8 +97,11 @@ __device__ __forceinline__ int lane_id() {
   return l;
 }
 
+// One wave publishes what it has written with agent_store: the stores have
+// arrived past the caches that the XCDs do not share once vmcnt is back at
+// zero.  (A release fence instead writes back a whole L2 per tile.)
 __device__ __forceinline__ void publish(int* f) {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (threadIdx.x == 0) __hip_atomic_store(f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -310,6 +327,7 @@ __device__ __forceinline__ void load_tile32(double4_t (&acc)[2][2], const double
       for (int r = 0; r < 4; ++r) acc[bm][bn][r] = M[(16 * bm + kq + 4 * r) * ld + 16 * bn + mrow];
 }
 
+template <bool AG = false>
 __device__ __forceinline__ void store_tile32(const double4_t (&acc)[2][2], double* M, size_t ld) {
   const int lane = lane_id(), mrow = lane & 15, kq = lane >> 4;
 #pragma unroll
@@ -317,7 +335,11 @@ __device__ __forceinline__ void store_tile32(const double4_t (&acc)[2][2], doubl
 #pragma unroll
     for (int bn = 0; bn < 2; ++bn)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) M[(16 * bm + kq + 4 * r) * ld + 16 * bn + mrow] = acc[bm][bn][r];
+      for (int r = 0; r < 4; ++r) {
+        double* p = M + (16 * bm + kq + 4 * r) * ld + 16 * bn + mrow;
+        if (AG) agent_store(p, acc[bm][bn][r]);
+        else *p = acc[bm][bn][r];
+      }
 }
 
 // 32 x 32 tile in LDS without padding, column index XOR-swizzled by row so
@@ -473,33 +495,6 @@ __device__ __forceinline__ void fwd_block(const double* Li, double* yb) {
   if (lane < NB) yb[c] = v;
 }
 
-// A run of published tiles of a tile's k-loop: the number of consecutive
-// k' = k, k + 1, ... (at most 32, below kend) whose flags (i, k') and (j, k')
-// are both set, from one vector load of 64 flags (relaxed; the caller issues
-// the acquire fence once for the whole run).
-__device__ __forceinline__ int ready_run(const int* fi, const int* fj, int k, int kend) {
-  const int lane = threadIdx.x & 63, off = lane & 31;
-  const int* f = lane < 32 ? fi : fj;
-  const int v = (k + off < kend) ? load_flag(f + k + off) : 0;
-  const unsigned long long miss = __ballot(v == 0);
-  const unsigned comb = (unsigned)miss | (unsigned)(miss >> 32);
-  return comb ? __builtin_ctz(comb) : 32;
-}
-
-// Wait (whole wave) until *f is set, without a fence.  false: the batch was aborted.
-__device__ __forceinline__ bool spin_flag(const int* f, int* sync) {
-  int spins = 0;
-  while (__builtin_amdgcn_readfirstlane(load_flag(f)) == 0) {
-    if (__builtin_amdgcn_readfirstlane(load_flag(sync + 1)) != 0) return false;
-    if (++spins > kSpinLimit) {
-      if (threadIdx.x == 0) __hip_atomic_store(sync + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return false;
-    }
-    __builtin_amdgcn_s_sleep(2);
-  }
-  return true;
-}
-
 // MFMA operands of one update X -= L_ik L_jk^T: lane supplies A[m][q] = L_ik[m][q]
 // (negated) and B[q][n] = L_jk[n][q] for its 16 rows and 4-column slices
 __device__ __forceinline__ void load_update(double (&a)[2][8], double (&b)[2][8], const double* Li, const double* Lj,
@@ -535,39 +530,64 @@ __device__ __forceinline__ void mfma_update_diag(double4_t (&acc)[2][2], const d
   }
 }
 
-// k-loop of a dataflow ticket over [k, kend): X -= L_ik L_jk^T, and with PAIR
-// also Y += L_ik L_ik^T (ONLY2: Y alone; the operand a = -L_ik serves as both
-// MFMA inputs, so Y holds the negated diagonal update), over runs of
-// published k with one acquire per run and the operands of k + 1 loaded while
-// the MFMAs of k run.  false: the batch was aborted.
+// k-loop of a dataflow ticket over the columns k in [kbeg, kend):
+// X -= L_ik L_jk^T, and with PAIR also Y += L_ik L_ik^T (ONLY2: Y alone; the
+// operand a = -L_ik serves as both MFMA inputs, so Y holds the negated diagonal
+// update).  The columns are taken in the order in which their chains reach them
+// (ord, positions p .. pend - 1; columns outside the range are passed over): in
+// the order of their index a row behind several parts would finish with one
+// before it looked at the next (512-keyframe pose graph: 117 us between the last
+// column of the parts and the first of the rows behind them).  The flags of 32
+// columns (lanes 0-31: row i, 32-63: row j) are read at once; a run of published
+// ones takes one acquire, with the operands of the next column loaded while the
+// MFMAs of this one run.  false: the batch was aborted.
 template <bool PAIR, bool ONLY2>
 __device__ __forceinline__ bool df_kloop(double4_t (&acc)[2][2], double4_t (&acc2)[2][2], const double* Ri,
-                                         const double* Rj, size_t npad, const int* fi, const int* fj, int k, int kend,
-                                         int* sync) {
+                                         const double* Rj, size_t npad, const int* fi, const int* fj, const int* ord,
+                                         int p, int pend, int kbeg, int kend, int* sync, bool near) {
   auto step = [&](const double (&a)[2][8], const double (&b)[2][8]) {
     if (!ONLY2) mfma_update(acc, a, b);
     if (PAIR || ONLY2) mfma_update_diag(acc2, a);
   };
-  while (k < kend) {
-    const int run = ready_run(fi, fj, k, kend);
+  if (kbeg >= kend) return true;
+  while (p < pend) {
+    const int lane = lane_id(), at = p + (lane & 31);
+    const int kk = at < pend ? ord[at] : -1;
+    const bool need = kk >= kbeg && kk < kend;
+    const int v = need ? load_flag((lane < 32 ? fi : fj) + kk) : 1;
+    const unsigned long long miss = __ballot(v == 0);
+    const unsigned comb = (unsigned)miss | (unsigned)(miss >> 32);
+    const int run = comb ? __builtin_ctz(comb) : 32;
     if (run == 0) {
-      if (!spin_flag(fi + k, sync)) return false;
-      if (fj != fi && !spin_flag(fj + k, sync)) return false;
+      const int k = __builtin_amdgcn_readfirstlane(kk);
+      if (!spin_flag(fi + k, sync, near)) return false;
+      if (fj != fi && !spin_flag(fj + k, sync, near)) return false;
       continue;
     }
+    p += run;
+    unsigned todo = (unsigned)__ballot(need) & (run < 32 ? (1u << run) - 1u : ~0u);
+    if (!todo) continue;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    const int ke = k + run;
+    // the next column of the run, -1 at its end
+    auto next = [&]() {
+      if (!todo) return -1;
+      const int k = __builtin_amdgcn_readlane(kk, __builtin_ctz(todo));
+      todo &= todo - 1;
+      return k;
+    };
     double a0[2][8], b0[2][8], a1[2][8], b1[2][8];
+    int k = next();
     load_update(a0, b0, Ri + NB * k, Rj + NB * k, npad);
-    for (; k < ke; k += 2) {
-      const bool has1 = k + 1 < ke;
-      if (has1) load_update(a1, b1, Ri + NB * (k + 1), Rj + NB * (k + 1), npad);
+    while (true) {
+      k = next();
+      if (k >= 0) load_update(a1, b1, Ri + NB * k, Rj + NB * k, npad);
       step(a0, b0);
-      if (!has1) { ++k; break; }
-      if (k + 2 < ke) load_update(a0, b0, Ri + NB * (k + 2), Rj + NB * (k + 2), npad);
+      if (k < 0) break;
+      k = next();
+      if (k >= 0) load_update(a0, b0, Ri + NB * k, Rj + NB * k, npad);
       step(a1, b1);
+      if (k < 0) break;
     }
-    k = ke;
   }
   return true;
 }
@@ -619,6 +639,7 @@ __global__ void __launch_bounds__(64) k_chol_df(DevPlan D, int ntickets, double*
     const int ij = D.chol_tiles[2 * t + 1];
     const bool pair = (ij & kPairTicket) != 0;
     const int i = (ij >> 16) & 0x3fff, j = ij & 0xffff;
+    const bool near = i - j <= 2;
     const WinDev& W = D.win[w];
     const int npad = W.npad, nblk = W.nblk;
     double* A = Aall + W.A_off;
@@ -632,8 +653,14 @@ __global__ void __launch_bounds__(64) k_chol_df(DevPlan D, int ntickets, double*
     double4_t acc[2][2], acc2[2][2];
     load_tile32(acc, Ri + NB * j, npad);
     const int k1 = max(fc[i], fc[j]);
+    // the columns in chain order: those of a row start at its beg, those before
+    // column j's successors end at its end
+    const int* ord = fc + nblk + 1;
+    const int pend = ord[nblk + j], pi = ord[2 * nblk + i], pj = max(pi, ord[2 * nblk + j]);
     if (!pair) {
-      if (!df_kloop<false, false>(acc, acc2, Ri, Rj, npad, fl + i * nblk, fl + j * nblk, k1, j, sync)) return;
+      if (!df_kloop<false, false>(acc, acc2, Ri, Rj, npad, fl + i * nblk, fl + j * nblk, ord, pj, pend, k1, j, sync,
+                                  near))
+        return;
     } else {
       // and X2 = S_ii - sum_{k < j} L_ik L_ik^T alongside (k >= fc[i]), as
       // its negative -S_ii + sum L_ik L_ik^T
@@ -642,8 +669,12 @@ __global__ void __launch_bounds__(64) k_chol_df(DevPlan D, int ntickets, double*
       for (int bm = 0; bm < 2; ++bm)
 #pragma unroll
         for (int bn = 0; bn < 2; ++bn) acc2[bm][bn] = -acc2[bm][bn];
-      if (!df_kloop<true, true>(acc, acc2, Ri, Ri, npad, fl + i * nblk, fl + i * nblk, fc[i], k1, sync)) return;
-      if (!df_kloop<true, false>(acc, acc2, Ri, Rj, npad, fl + i * nblk, fl + j * nblk, k1, j, sync)) return;
+      if (!df_kloop<true, true>(acc, acc2, Ri, Ri, npad, fl + i * nblk, fl + i * nblk, ord, pi, pend, fc[i], k1, sync,
+                                near))
+        return;
+      if (!df_kloop<true, false>(acc, acc2, Ri, Rj, npad, fl + i * nblk, fl + j * nblk, ord, pj, pend, k1, j, sync,
+                                 near))
+        return;
 #pragma unroll
       for (int bm = 0; bm < 2; ++bm)
 #pragma unroll
@@ -659,15 +690,15 @@ __global__ void __launch_bounds__(64) k_chol_df(DevPlan D, int ntickets, double*
 #pragma unroll
       for (int it = 0; it < 16; ++it) {
         const int e = lane + 64 * it;
-        Lo[e] = Lt[(e >> 5) * LD + (e & 31)];
+          agent_store(Lo + e, Lt[(e >> 5) * LD + (e & 31)]);
       }
       publish(fl + j * nblk + j);
     } else {
-      if (!wait_flag(fl + j * nblk + j, sync)) return;
+      if (!wait_flag(fl + j * nblk + j, sync, near)) return;
       // L_ij = X L_jj^-T: A[m][q] = X[m][q], B[q][n] = Linv[n][q]
       double4_t out[2][2];
       solve_panel(out, T, Lv + (size_t)j * NB * NB);
-      store_tile32(out, A + (size_t)(NB * i) * npad + NB * j, npad);
+      store_tile32<true>(out, A + (size_t)(NB * i) * npad + NB * j, npad);
       publish(fl + i * nblk + j);
       if (pair) {
         // X2 -= L_ij L_ij^T (L_ij through LDS into the operand layout), then
@@ -684,7 +715,7 @@ __global__ void __launch_bounds__(64) k_chol_df(DevPlan D, int ntickets, double*
 #pragma unroll
         for (int it = 0; it < 16; ++it) {
           const int e = lane + 64 * it;
-          Lo[e] = Lt[(e >> 5) * LD + (e & 31)];
+          agent_store(Lo + e, Lt[(e >> 5) * LD + (e & 31)]);
         }
         publish(fl + i * nblk + i);
       }
@@ -981,12 +1012,12 @@ __global__ void __launch_bounds__(256) k_chol_bs(DevPlan D, int t0, int nbs, con
     const int t = tk;
     __syncthreads();
     if (t >= nbs) return;
-    // two block columns per ticket: c and c - 1 (when c > 0), so that the
+    // two block columns per ticket, c and c - 1 (of one chain), so that the
     // chain of the back-substitution hands over between workgroups at every
     // second block only
     const int w = D.chol_tiles[2 * (t0 + t)];
     const int c = D.chol_tiles[2 * (t0 + t) + 1] & 0xffff;
-    const bool two = c > 0;
+    const bool two = (D.chol_tiles[2 * (t0 + t) + 1] & kPairTicket) != 0;
     const int cb = c - 1;
     const WinDev& W = D.win[w];
     const int npad = W.npad, nblk = W.nblk;
@@ -1034,7 +1065,7 @@ __global__ void __launch_bounds__(256) k_chol_bs(DevPlan D, int t0, int nbs, con
       const unsigned long long miss = __ballot(ready == 0);
       const int run = min((int)(miss ? __builtin_ctzll(miss) : 32), b - c);
       if (run == 0) {
-        if (!aborted) aborted = !spin_flag(xf + b, sync);
+        if (!aborted) aborted = !spin_flag(xf + b, sync, b <= c + 2);
         if (aborted) {
           b = c;                      // the batch was aborted: no more waits
           break;

@@ -34,17 +34,6 @@ __device__ __forceinline__ bool coord_active(const OptsDev& o, int a, int ra, in
   return true;
 }
 
-// Values that one workgroup hands to another inside a launch: stored and loaded
-// at agent scope one by one, past the caches that the XCDs do not share.  (A
-// release fence per inertial factor instead would write back a whole L2 each.)
-__device__ __forceinline__ void agent_store(double* p, double v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <bool AG>
-__device__ __forceinline__ double agent_load(const double* p) {
-  return AG ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
-}
-
 // inertial part of the entry ((a, ra), (b, cb)) of B: the blocks of the
 // factors (a - 1, a) and (a, a + 1) of the window (Hw: [F][30][30]).  AG: in
 // the launch that forms them.

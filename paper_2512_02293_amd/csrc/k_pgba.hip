@@ -434,7 +434,9 @@ __global__ void k_assemble_pg(int n_fixed, double lambda, DevPlan D, const doubl
     // rows -> keyframes (the window's order of the reduced system)
     const int mr = D.row_map[W.x_off + r], mc = D.row_map[W.x_off + c];
     const int a = mr >> 8, ra = mr & 255, b = mc >> 8, cb = mc & 255;
-    if (pg_active(a, n_fixed) && pg_active(b, n_fixed)) {
+    if (mr < 0 || mc < 0) {
+      val = (r == c) ? 1.0 : 0.0;              // a row between two parts
+    } else if (pg_active(a, n_fixed) && pg_active(b, n_fixed)) {
       double bd = 0.0;
       const int p0 = poff[a * N + b], p1 = poff[a * N + b + 1];
       for (int it = p0; it < p1; ++it) {
@@ -451,7 +453,7 @@ __global__ void k_assemble_pg(int n_fixed, double lambda, DevPlan D, const doubl
   } else if (r == npad && c < n) {
     const int mc = D.row_map[W.x_off + c];
     const int b = mc >> 8, cb = mc & 255;
-    if (pg_active(b, n_fixed)) {
+    if (mc >= 0 && pg_active(b, n_fixed)) {
       const int p0 = poff[b * N + b], p1 = poff[b * N + b + 1];
       for (int it = p0; it < p1; ++it) val += ZV[D.pair_zb[it] + cb];
     }

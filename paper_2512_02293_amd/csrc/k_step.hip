@@ -1716,7 +1716,9 @@ __global__ void k_assemble(OptsDev o, DevPlan D, const double* __restrict__ Z, c
     // rows -> keyframes (the window's order of the reduced system)
     const int mr = D.row_map[W.x_off + r], mc = D.row_map[W.x_off + c];
     const int a = mr >> 8, ra = mr & 255, b = mc >> 8, cb = mc & 255;
-    if (coord_active(o, a, ra, N) && coord_active(o, b, cb, N)) {
+    if (mr < 0 || mc < 0) {
+      val = (r == c) ? 1.0 : 0.0;              // a row between two parts
+    } else if (coord_active(o, a, ra, N) && coord_active(o, b, cb, N)) {
       double bd = 0.0;
       if (ra < 6 && cb < 6) {
         // the pair blocks of (a, b) in list order, eight gathers in flight
@@ -1760,7 +1762,7 @@ __global__ void k_assemble(OptsDev o, DevPlan D, const double* __restrict__ Z, c
   } else if (r == npad && c < n) {
     const int mc = D.row_map[W.x_off + c];
     const int b = mc >> 8, cb = mc & 255;
-    if (coord_active(o, b, cb, N)) {
+    if (mc >= 0 && coord_active(o, b, cb, N)) {
       if (cb < 6) {
         const int p0 = poff[b * N + b], p1 = poff[b * N + b + 1];
         for (int it0 = p0; it0 < p1; it0 += 8) {

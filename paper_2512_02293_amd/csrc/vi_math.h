@@ -18,6 +18,17 @@ __device__ __forceinline__ double rsqrt_refined(double v) {
   return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
 }
 
+// Values that one workgroup hands to another inside a launch: stored and loaded
+// at agent scope one by one, past the caches that the XCDs do not share.  (A
+// release fence instead would write back a whole L2.)
+__device__ __forceinline__ void agent_store(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <bool AG>
+__device__ __forceinline__ double agent_load(const double* p) {
+  return AG ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+
 // A pointer that was itself loaded from memory, declared as one to global
 // memory: through the generic type its loads are flat ones, which count as LDS
 // operations too, so that every wait for LDS waits for them.
