@@ -250,7 +250,7 @@ std::vector<int> rcm_order(int N, const std::vector<std::vector<int>>& adj) {
 // through both at once, and T comes last.  levels > 1: L and R again.  Appends
 // to out, -1 where the next keyframe has to start a tile of its own (with a
 // tile shared between two parts the second would wait for the first).
-constexpr int kCutLevels = 2;                            // at most 4 independent parts
+constexpr int kCutLevels = 3;                            // at most 8 independent parts (4: 474 instead of 445 us below)
 constexpr int kCutPad = ((1 << kCutLevels) - 1) * (kCholNB - 1);   // rows that they may skip
 
 void dissect(const std::vector<int>& seq, int levels, const std::vector<int>& dim,
@@ -385,45 +385,65 @@ CondLayout cond_layout(int N, bool bias_global) {
   return C;
 }
 
-// tile envelope (nblk + 1 entries, the last one the right-hand-side row), the
-// tile-update count of the dataflow factorisation over it and the tile band
-struct Envelope {
-  std::vector<int> fc;
-  long long work = 0;
+// What an order of the keyframes makes of the reduced system: on the
+// one-workgroup path the tile band, on the dataflow path the nonzero tiles of
+// the factor, its chains of block columns and its tile updates
+struct Order {
   int band = 0;
+  long long work = 0;
   int chain = 0;             // longest chain of block columns that wait for one another
   std::vector<int> depth;    // position of each block column in its chain
+  std::vector<uint32_t> nz;  // by block row (the last one the right-hand side): a bit per nonzero tile
+  bool has(int nw, int i, int j) const { return (nz[(size_t)i * nw + (j >> 5)] >> (j & 31)) & 1u; }
 };
 
-Envelope tile_envelope(const std::vector<int>& fcs, int n, int nblk) {
-  Envelope E;
-  E.fc.assign(nblk + 1, 0);
+int tile_band(const std::vector<int>& fcs, int nblk) {
   int wsc = 0;
-  for (int i = 0; i < nblk; ++i) {
-    int f = i;
-    for (int r = i * kCholNB; r < std::min(n, (i + 1) * kCholNB); ++r) {
-      f = std::min(f, fcs[r] / kCholNB);
-      wsc = std::max(wsc, r - fcs[r]);
-    }
-    E.fc[i] = f;
-  }
-  E.fc[nblk] = 0;
-  for (int i = 0; i <= nblk; ++i)
-    for (int j = E.fc[i]; j <= std::min(i, nblk - 1); ++j) E.work += 1 + (j - std::max(E.fc[i], E.fc[j]));
-  E.band = std::min(nblk - 1, (wsc + kCholNB - 1) / kCholNB);
-  E.depth.assign(nblk, 1);
-  for (int j = 0; j < nblk; ++j) {
-    for (int k = E.fc[j]; k < j; ++k) E.depth[j] = std::max(E.depth[j], E.depth[k] + 1);
-    E.chain = std::max(E.chain, E.depth[j]);
-  }
-  return E;
+  for (int r = 0; r < (int)fcs.size(); ++r) wsc = std::max(wsc, r - fcs[r]);
+  return std::min(nblk - 1, (wsc + kCholNB - 1) / kCholNB);
 }
 
-// Relative time of the dataflow factorisation over an envelope: its block
-// columns take about 10 us each one after the other, beside which the tile
+// The tiles of the factor that are not zero: those of S (couplings, the blocks
+// of the keyframes), the right-hand-side row, and what the elimination fills
+// in; with them the chains and the work of the dataflow factorisation.
+void tile_fill(const std::vector<int>& dim, const std::vector<Coupling>& cpl, const std::vector<int>& off, int nblk,
+               Order& E) {
+  const int nw = (nblk + 31) / 32;
+  E.nz.assign((size_t)(nblk + 1) * nw, 0u);
+  auto set = [&](int i, int j) { E.nz[(size_t)i * nw + (j >> 5)] |= 1u << (j & 31); };
+  auto block = [&](int r0, int rn, int c0, int cn) {
+    for (int i = r0 / kCholNB; i <= (r0 + rn - 1) / kCholNB; ++i)
+      for (int j = c0 / kCholNB; j <= (c0 + cn - 1) / kCholNB; ++j) set(std::max(i, j), std::min(i, j));
+  };
+  for (size_t a = 0; a < dim.size(); ++a) block(off[a], dim[a], off[a], dim[a]);
+  for (const Coupling& c : cpl) block(off[c.a], c.full_a ? dim[c.a] : 6, off[c.b], c.full_b ? dim[c.b] : 6);
+  for (int j = 0; j < nblk; ++j) {
+    set(j, j);
+    set(nblk, j);
+  }
+  // eliminating column j couples the rows below it in that column
+  std::vector<int> rows;
+  E.depth.assign(nblk, 1);
+  E.chain = 0;
+  E.work = 0;
+  for (int j = 0; j < nblk; ++j) {
+    rows.clear();
+    for (int i = j + 1; i <= nblk; ++i)
+      if (E.has(nw, i, j)) rows.push_back(i);
+    for (size_t p = 0; p < rows.size(); ++p)
+      for (size_t q = 0; q <= p; ++q)
+        if (rows[q] < nblk) set(rows[p], rows[q]);
+    for (int i : rows)
+      if (i < nblk) E.depth[i] = std::max(E.depth[i], E.depth[j] + 1);
+    E.chain = std::max(E.chain, E.depth[j]);
+    E.work += (long long)rows.size() * (rows.size() + 1) / 2 + rows.size() + 1;
+  }
+}
+
+// Relative time of the dataflow factorisation: its block columns take about 10 us each one after the other, beside which the tile
 // updates of a column (about 1 us on one of some 250 waves at a time) hardly
 // count.
-double dataflow_cost(const Envelope& E) { return E.chain + (double)E.work / 2500.0; }
+double dataflow_cost(const Order& E) { return E.chain + (double)E.work / 2500.0; }
 
 vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool use_imu, bool bias_global) {
   P = Plan();
@@ -545,7 +565,7 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
   // per window: reduced system and gather lists of its assembly.  Pose block
   // (a, b) <- Z blocks of every source whose touched set contains a and b.
   size_t A_off = 0, L_off = 0, x_off = 0;
-  std::vector<std::vector<int>> depth(nw);
+  std::vector<Order> envs(nw);
   size_t A_cap[2] = {0, 0}, L_cap[2] = {0, 0}, x_cap[2] = {0, 0}, f_cap[2] = {0, 0}, c_cap[2] = {0, 0},
          s_cap[2] = {0, 0};
   for (int w = 0; w < nw; ++w) {
@@ -605,26 +625,31 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
     // Natural order unless another one suits the factorisation path of this
     // window better: the reverse Cuthill-McKee order, by the band on the
     // one-workgroup path, and on the dataflow path by its cost, there also
-    // either of them dissected into 2 or 4 parts.  The keyframe with the shared
+    // either of them dissected into 2, 4 or 8 parts.  The keyframe with the shared
     // bias couples with every other one: it stays out of the dissection and
     // comes last.
     int n0 = 0;
     for (int d : dim) n0 += d;
     std::vector<int> seq(W.N), off, fcs;
     for (int a = 0; a < W.N; ++a) seq[a] = a;
-    Envelope env;
-    auto measure = [&](const std::vector<int>& q, std::vector<int>& o, Envelope& e) {
+    Order env;
+    const bool small_path = (n0 + kCholNB - 1) / kCholNB * kCholNB <= kCholSmallMaxNpad;
+    auto measure = [&](const std::vector<int>& q, std::vector<int>& o, Order& e) {
       const int n = sequence_rows(q, dim, o);
-      scalar_envelope(dim, cpl, o, n, fcs);
-      e = tile_envelope(fcs, n, (n + kCholNB - 1) / kCholNB);
+      const int nblk = (n + kCholNB - 1) / kCholNB;
+      if (small_path) {
+        scalar_envelope(dim, cpl, o, n, fcs);
+        e.band = tile_band(fcs, nblk);
+      } else {
+        tile_fill(dim, cpl, o, nblk, e);
+      }
       return n;
     };
     W.n = measure(seq, off, env);
-    const bool small_path = (n0 + kCholNB - 1) / kCholNB * kCholNB <= kCholSmallMaxNpad;
-    if (env.band > 0) {
+    if (!small_path || env.band > 0) {
       auto consider = [&](const std::vector<int>& q) {
         std::vector<int> off2;
-        Envelope env2;
+        Order env2;
         const int n2 = measure(q, off2, env2);
         if (small_path ? env2.band < env.band : dataflow_cost(env2) < dataflow_cost(env)) {
           W.n = n2;
@@ -709,24 +734,29 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
       P.cond_size += cond.doubles;
     }
     W.band = env.band;
-    depth[w] = env.depth;
-    W.fc_off = (int)P.chol_fc.size();
-    P.chol_fc.insert(P.chol_fc.end(), env.fc.begin(), env.fc.end());
-    // behind it the block columns in chain order, for each column the number of
-    // them up to its own position in its chain, and for each block row (with the
-    // right-hand side) the position of the first one it needs
-    std::vector<int32_t> ord(W.nblk), pos(W.nblk);
-    std::iota(ord.begin(), ord.end(), 0);
-    std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return env.depth[x] < env.depth[y]; });
-    for (int p = 0; p < W.nblk; ++p) pos[ord[p]] = p;
-    P.chol_fc.insert(P.chol_fc.end(), ord.begin(), ord.end());
-    for (int j = 0; j < W.nblk; ++j)
-      P.chol_fc.push_back((int32_t)(std::upper_bound(ord.begin(), ord.end(), env.depth[j],
-                                                     [&](int d, int k) { return d < env.depth[k]; }) - ord.begin()));
-    for (int i = 0; i <= W.nblk; ++i) {
-      int32_t beg = W.nblk;
-      for (int k = env.fc[i]; k < std::min(i, W.nblk); ++k) beg = std::min(beg, pos[k]);
-      P.chol_fc.push_back(beg);
+    envs[w] = env;
+    // the dataflow path's table: the block columns in chain order, for each
+    // column the number of them up to its own position in its chain, for each
+    // block row (with the right-hand side) the position of the first one it
+    // needs, and the nonzero tiles
+    W.tab_off = (int)P.chol_tab.size();
+    if (!small_path) {
+      const int nw = (W.nblk + 31) / 32;
+      std::vector<int32_t> ord(W.nblk), pos(W.nblk);
+      std::iota(ord.begin(), ord.end(), 0);
+      std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return env.depth[x] < env.depth[y]; });
+      for (int p = 0; p < W.nblk; ++p) pos[ord[p]] = p;
+      P.chol_tab.insert(P.chol_tab.end(), ord.begin(), ord.end());
+      for (int j = 0; j < W.nblk; ++j)
+        P.chol_tab.push_back((int32_t)(std::upper_bound(ord.begin(), ord.end(), env.depth[j],
+                                                       [&](int d, int k) { return d < env.depth[k]; }) - ord.begin()));
+      for (int i = 0; i <= W.nblk; ++i) {
+        int32_t beg = W.nblk;
+        for (int k = 0; k < std::min(i, W.nblk); ++k)
+          if (env.has(nw, i, k)) beg = std::min(beg, pos[k]);
+        P.chol_tab.push_back(beg);
+      }
+      for (uint32_t v : env.nz) P.chol_tab.push_back((int32_t)v);
     }
     // this window's table: entries pair_base .. pair_base + N*N (the last one is its end)
     W.pair_base = (int)P.pair_off.size();
@@ -748,7 +778,7 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
   for (int w = 0; w < nw; ++w) {
     if (P.win[w].npad <= kCholSmallMaxNpad) continue;
     for (int j = 0; j < P.win[w].nblk; ++j) {
-      const size_t d = (size_t)depth[w][j];
+      const size_t d = (size_t)envs[w].depth[j];
       if (at.size() <= d) at.resize(d + 1);
       at[d].push_back({w, j});
     }
@@ -757,18 +787,19 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
     for (const auto& wj : cols) {
       const int w = wj.first, j = wj.second;
       const WinDev& W = P.win[w];
-      const int32_t* fc = &P.chol_fc[W.fc_off];
+      const Order& E = envs[w];
+      const int nw = (W.nblk + 31) / 32;
       // the diagonal tile, unless the ticket of tile (j, j - 1) carries it: tile
       // (j + 1, j) carries the diagonal tile j + 1 (kPairTicket) when column
       // j + 1 follows on j in its chain (else a longer chain ends in it);
-      // tiles outside the envelope are zero in S and in L
-      auto paired = [&](int c) { return fc[c] < c && depth[w][c] == depth[w][c - 1] + 1; };
+      // zero tiles have none
+      auto paired = [&](int c) { return c > 0 && E.has(nw, c, c - 1) && E.depth[c] == E.depth[c - 1] + 1; };
       if (!paired(j)) {
         P.chol_tiles.push_back(w);
         P.chol_tiles.push_back((j << 16) | j);
       }
       for (int i = j + 1; i <= W.nblk; ++i) {
-        if (fc[i] > j) continue;
+        if (!E.has(nw, i, j)) continue;
         P.chol_tiles.push_back(w);
         P.chol_tiles.push_back((i << 16) | j | ((i == j + 1 && i < W.nblk && paired(i)) ? kPairTicketFlag : 0));
       }
@@ -783,7 +814,7 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
     for (int w = 0; w < nw; ++w) {
       const int c = next[w];
       if (c < 0) continue;
-      const bool two = c > 0 && P.chol_fc[P.win[w].fc_off + c] < c;
+      const bool two = c > 0 && envs[w].has((P.win[w].nblk + 31) / 32, c, c - 1);
       P.chol_tiles.push_back(w);
       P.chol_tiles.push_back(c | (two ? kPairTicketFlag : 0));
       next[w] = c - (two ? 2 : 1);
@@ -793,6 +824,7 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
   P.n_bs = (int)(P.chol_tiles.size() / 2) - P.n_tickets;
   P.row_map.resize(x_off, -1);
   if (P.gram_map.empty()) P.gram_map.push_back(0);
+  if (P.chol_tab.empty()) P.chol_tab.push_back(0);
   P.A_size = std::max({A_off, A_cap[0], A_cap[1]});
   P.Linv_size = std::max({L_off, L_cap[0], L_cap[1]});
   P.x_size = std::max({x_off, x_cap[0], x_cap[1]});
@@ -892,7 +924,7 @@ vi_status upload_plan(vi_ctx* ctx) {
                         {&P.z_off, &D.z_off}, {&P.zb_off, &D.zb_off}, {&P.pair_off, &D.pair_off},
                         {&P.pair_z, &D.pair_z}, {&P.pair_zb, &D.pair_zb}, {&P.chol_tiles, &D.chol_tiles},
                         {&P.rel_ii, &D.rel_ii}, {&P.rel_jj, &D.rel_jj}, {&P.rel_z, &D.rel_z}, {&P.rel_zb, &D.rel_zb},
-                        {&P.kf_off, &D.kf_off}, {&P.row_map, &D.row_map}, {&P.chol_fc, &D.chol_fc},
+                        {&P.kf_off, &D.kf_off}, {&P.row_map, &D.row_map}, {&P.chol_tab, &D.chol_tab},
                         {&P.kf_seg, &D.kf_seg}, {&P.f_seg, &D.f_seg}, {&P.gram_map, &D.gram_map}, {&segs, &dsegs}};
   size_t total = align256(sizeof(WinDev) * P.n_win);
   for (const Part& p : parts) total += align256(std::max<size_t>(p.v->size(), 1) * sizeof(int32_t));

@@ -15,9 +15,10 @@
 //                                              acquire per run of published k)
 //   i == j : factor and invert X (register-resident 8 x 8 leaves joined by MFMA);
 //   i != j : L_ij = X L_jj^-T                 (FP64 MFMA)
-// and publishes the result with a release flag.  Tiles are handed out by an
-// atomic ticket counter in column-major order (column j, then window, then
-// row i), and a tile only ever waits for tiles of smaller tickets, which were
+// and publishes the result with a flag; k runs over the columns in which both
+// tiles are nonzero in the factor, zero tiles are not formed at all.  Tiles are
+// handed out by an atomic ticket counter in chain order (the position of column
+// j in its chain, then window, column and row i), and a tile only ever waits for tiles of smaller tickets, which were
 // taken by running workgroups: every wait ends without any assumption on
 // how many workgroups are resident.  Every wait is also bounded: past the
 // limit the batch is aborted (VI_EDEVICE) and every workgroup exits.
@@ -530,62 +531,68 @@ __device__ __forceinline__ void mfma_update_diag(double4_t (&acc)[2][2], const d
   }
 }
 
-// k-loop of a dataflow ticket over the columns k in [kbeg, kend):
-// X -= L_ik L_jk^T, and with PAIR also Y += L_ik L_ik^T (ONLY2: Y alone; the
-// operand a = -L_ik serves as both MFMA inputs, so Y holds the negated diagonal
-// update).  The columns are taken in the order in which their chains reach them
-// (ord, positions p .. pend - 1; columns outside the range are passed over): in
-// the order of their index a row behind several parts would finish with one
-// before it looked at the next (512-keyframe pose graph: 117 us between the last
-// column of the parts and the first of the rows behind them).  The flags of 32
-// columns (lanes 0-31: row i, 32-63: row j) are read at once; a run of published
-// ones takes one acquire, with the operands of the next column loaded while the
-// MFMAs of this one run.  false: the batch was aborted.
-template <bool PAIR, bool ONLY2>
+// k-loop of a dataflow ticket over the columns k < j: X -= L_ik L_jk^T where both
+// tiles are nonzero (bits of rows i and j in ni, nj), and with PAIR also
+// Y += L_ik L_ik^T wherever L_ik is (a = -L_ik serves as both MFMA inputs, so Y
+// holds the negated diagonal update).  The columns are taken in the order in
+// which their chains reach them (ord, positions p .. pend - 1): in the order of
+// their index a row behind several parts would finish with one before it looked
+// at the next (512-keyframe pose graph: 117 us between the last column of the
+// parts and the first of the rows behind them).  The flags of 32 columns (lanes
+// 0-31: row i, 32-63: row j) are read at once; a run of published ones takes one
+// acquire, with the operands of the next column loaded while the MFMAs of this
+// one run.  false: the batch was aborted.
+template <bool PAIR>
 __device__ __forceinline__ bool df_kloop(double4_t (&acc)[2][2], double4_t (&acc2)[2][2], const double* Ri,
                                          const double* Rj, size_t npad, const int* fi, const int* fj, const int* ord,
-                                         int p, int pend, int kbeg, int kend, int* sync, bool near) {
-  auto step = [&](const double (&a)[2][8], const double (&b)[2][8]) {
-    if (!ONLY2) mfma_update(acc, a, b);
-    if (PAIR || ONLY2) mfma_update_diag(acc2, a);
-  };
-  if (kbeg >= kend) return true;
+                                         const int* ni, const int* nj, int p, int pend, int j, int* sync, bool near) {
   while (p < pend) {
     const int lane = lane_id(), at = p + (lane & 31);
-    const int kk = at < pend ? ord[at] : -1;
-    const bool need = kk >= kbeg && kk < kend;
-    const int v = need ? load_flag((lane < 32 ? fi : fj) + kk) : 1;
+    const int kk = at < pend ? ord[at] : j;
+    const bool in_i = kk < j && (((unsigned)ni[kk >> 5] >> (kk & 31)) & 1u) != 0;
+    const bool in_j = kk < j && (((unsigned)nj[kk >> 5] >> (kk & 31)) & 1u) != 0;
+    const bool both = in_i && in_j, need = PAIR ? in_i : both;
+    const bool wait = lane < 32 ? need : both;
+    const int v = wait ? load_flag((lane < 32 ? fi : fj) + kk) : 1;
     const unsigned long long miss = __ballot(v == 0);
     const unsigned comb = (unsigned)miss | (unsigned)(miss >> 32);
     const int run = comb ? __builtin_ctz(comb) : 32;
     if (run == 0) {
       const int k = __builtin_amdgcn_readfirstlane(kk);
       if (!spin_flag(fi + k, sync, near)) return false;
-      if (fj != fi && !spin_flag(fj + k, sync, near)) return false;
+      if ((miss >> 32) & 1ull)
+        if (!spin_flag(fj + k, sync, near)) return false;
       continue;
     }
     p += run;
     unsigned todo = (unsigned)__ballot(need) & (run < 32 ? (1u << run) - 1u : ~0u);
+    const unsigned xs = (unsigned)__ballot(both);
     if (!todo) continue;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    // the next column of the run, -1 at its end
-    auto next = [&]() {
+    // the next column of the run (-1 at its end) and whether X takes it
+    bool x0 = false, x1 = false;
+    auto next = [&](bool& x) {
       if (!todo) return -1;
-      const int k = __builtin_amdgcn_readlane(kk, __builtin_ctz(todo));
+      const int q = __builtin_ctz(todo);
       todo &= todo - 1;
-      return k;
+      x = (xs >> q) & 1u;
+      return __builtin_amdgcn_readlane(kk, q);
+    };
+    auto step = [&](const double (&a)[2][8], const double (&b)[2][8], bool x) {
+      if (!PAIR || x) mfma_update(acc, a, b);
+      if (PAIR) mfma_update_diag(acc2, a);
     };
     double a0[2][8], b0[2][8], a1[2][8], b1[2][8];
-    int k = next();
-    load_update(a0, b0, Ri + NB * k, Rj + NB * k, npad);
+    int k = next(x0);
+    load_update(a0, b0, Ri + NB * k, (!PAIR || x0 ? Rj : Ri) + NB * k, npad);
     while (true) {
-      k = next();
-      if (k >= 0) load_update(a1, b1, Ri + NB * k, Rj + NB * k, npad);
-      step(a0, b0);
+      k = next(x1);
+      if (k >= 0) load_update(a1, b1, Ri + NB * k, (!PAIR || x1 ? Rj : Ri) + NB * k, npad);
+      step(a0, b0, x0);
       if (k < 0) break;
-      k = next();
-      if (k >= 0) load_update(a0, b0, Ri + NB * k, Rj + NB * k, npad);
-      step(a1, b1);
+      k = next(x0);
+      if (k >= 0) load_update(a0, b0, Ri + NB * k, (!PAIR || x0 ? Rj : Ri) + NB * k, npad);
+      step(a1, b1, x1);
       if (k < 0) break;
     }
   }
@@ -645,35 +652,30 @@ __global__ void __launch_bounds__(64) k_chol_df(DevPlan D, int ntickets, double*
     double* A = Aall + W.A_off;
     double* Lv = Linvall + W.Linv_off;
     int* fl = flagsall + W.flag_off;
-    const int* fc = D.chol_fc + W.fc_off;
     const double* Ri = A + (size_t)(NB * i) * npad;
     const double* Rj = A + (size_t)(NB * j) * npad;
-    // X = S_ij - sum_k L_ik L_jk^T; L_ik and L_jk are zero left of the
-    // envelope (k < fc[i] or k < fc[j])
+    // X = S_ij - sum_k L_ik L_jk^T
     double4_t acc[2][2], acc2[2][2];
     load_tile32(acc, Ri + NB * j, npad);
-    const int k1 = max(fc[i], fc[j]);
-    // the columns in chain order: those of a row start at its beg, those before
-    // column j's successors end at its end
-    const int* ord = fc + nblk + 1;
+    // the columns in chain order: a row's first one at its beg, those before the
+    // successors of column j up to its end; bits of the nonzero tiles by row
+    const int* ord = D.chol_tab + W.tab_off;
     const int pend = ord[nblk + j], pi = ord[2 * nblk + i], pj = max(pi, ord[2 * nblk + j]);
+    const int nzw = (nblk + 31) / 32;
+    const int* nz = ord + 3 * nblk + 1;
+    const int *ni = nz + i * nzw, *nj = nz + j * nzw;
     if (!pair) {
-      if (!df_kloop<false, false>(acc, acc2, Ri, Rj, npad, fl + i * nblk, fl + j * nblk, ord, pj, pend, k1, j, sync,
-                                  near))
+      if (!df_kloop<false>(acc, acc2, Ri, Rj, npad, fl + i * nblk, fl + j * nblk, ord, ni, nj, pj, pend, j, sync, near))
         return;
     } else {
-      // and X2 = S_ii - sum_{k < j} L_ik L_ik^T alongside (k >= fc[i]), as
-      // its negative -S_ii + sum L_ik L_ik^T
+      // and X2 = S_ii - sum_{k < j} L_ik L_ik^T alongside, as its negative
+      // -S_ii + sum L_ik L_ik^T
       load_tile32(acc2, Ri + NB * i, npad);
 #pragma unroll
       for (int bm = 0; bm < 2; ++bm)
 #pragma unroll
         for (int bn = 0; bn < 2; ++bn) acc2[bm][bn] = -acc2[bm][bn];
-      if (!df_kloop<true, true>(acc, acc2, Ri, Ri, npad, fl + i * nblk, fl + i * nblk, ord, pi, pend, fc[i], k1, sync,
-                                near))
-        return;
-      if (!df_kloop<true, false>(acc, acc2, Ri, Rj, npad, fl + i * nblk, fl + j * nblk, ord, pj, pend, k1, j, sync,
-                                 near))
+      if (!df_kloop<true>(acc, acc2, Ri, Rj, npad, fl + i * nblk, fl + j * nblk, ord, ni, nj, pi, pend, j, sync, near))
         return;
 #pragma unroll
       for (int bm = 0; bm < 2; ++bm)
@@ -1025,7 +1027,11 @@ __global__ void __launch_bounds__(256) k_chol_bs(DevPlan D, int t0, int nbs, con
     const double* Lcc = Linvall + W.Linv_off + (size_t)c * NB * NB;
     double* x = xall + W.x_off;
     int* xf = flagsall + W.flag_off + (nblk + 1) * nblk;     // x_b published
-    const int* fc = D.chol_fc + W.fc_off;
+    // whether tile (b, c) of the factor is nonzero (bits by row behind the
+    // chain order)
+    const int nzw = (nblk + 31) / 32;
+    const int* nz = D.chol_tab + W.tab_off + 3 * nblk + 1;
+    auto has = [&](int b, int col) { return (((unsigned)nz[b * nzw + (col >> 5)] >> (col & 31)) & 1u) != 0; };
     bool aborted = load_flag(sync + 1) != 0;
     // columns q of L_cc^-1, of L_(c-1)(c-1)^-1 and of L_c,c-1 for the last
     // steps, loaded before any wait
@@ -1037,15 +1043,13 @@ __global__ void __launch_bounds__(256) k_chol_bs(DevPlan D, int t0, int nbs, con
         const double* Lbb = Linvall + W.Linv_off + (size_t)cb * NB * NB;
 #pragma unroll
         for (int r = 0; r < NB; ++r) lbb[r] = Lbb[r * NB + q];
-        const bool in_env = fc[c] <= cb;      // L_c,c-1 = 0 outside the envelope
 #pragma unroll
-        for (int r = 0; r < NB; ++r) lcb[r] = in_env ? A[(size_t)(NB * c + r) * npad + NB * cb + q] : 0.0;
+        for (int r = 0; r < NB; ++r) lcb[r] = A[(size_t)(NB * c + r) * npad + NB * cb + q];
       }
     }
     // t_c = y_c - sum_b L_bc^T x_b over b = nblk-1 .. c+1 (in that order),
-    // and the same sum for column c - 1, inside the envelope: the flags of up
-    // to 32 blocks are read at once (a block outside the envelope counts as
-    // ready) and every ready run is summed with one acquire and its loads in
+    // and the same sum for column c - 1, over the nonzero tiles: the flags of up
+    // to 32 blocks are read at once (a block of a zero tile counts as ready) and every ready run is summed with one acquire and its loads in
     // flight.  The tiles of block c + 1, whose x comes last (it waits for the
     // previous ticket), are loaded before any wait: the factor is final.
     double acc = 0.0, accb = 0.0;
@@ -1054,14 +1058,14 @@ __global__ void __launch_bounds__(256) k_chol_bs(DevPlan D, int t0, int nbs, con
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const size_t row = (size_t)(NB * (c + 1) + r8 + 8 * u) * npad;
-        vl[u] = fc[c + 1] <= c ? A[row + NB * c + q] : 0.0;
-        vlb[u] = (two && fc[c + 1] <= cb) ? A[row + NB * cb + q] : 0.0;
+        vl[u] = has(c + 1, c) ? A[row + NB * c + q] : 0.0;
+        vlb[u] = (two && has(c + 1, cb)) ? A[row + NB * cb + q] : 0.0;
       }
     }
     int b = nblk - 1;
     while (b > c) {
       const int bq = b - (lane & 31);
-      const int ready = (bq > c && fc[bq] <= c) ? load_flag(xf + bq) : 1;   // blocks outside the envelope: not needed
+      const int ready = (bq > c && has(bq, c)) ? load_flag(xf + bq) : 1;    // zero tiles: not needed
       const unsigned long long miss = __ballot(ready == 0);
       const int run = min((int)(miss ? __builtin_ctzll(miss) : 32), b - c);
       if (run == 0) {
@@ -1074,8 +1078,8 @@ __global__ void __launch_bounds__(256) k_chol_bs(DevPlan D, int t0, int nbs, con
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       for (const int bend = b - run; b > bend; --b) {
-        if (fc[b] > c) continue;      // L_bc = 0 outside the envelope (and L_b,c-1)
-        const bool use_b = two && fc[b] <= cb;
+        if (!has(b, c)) continue;     // L_bc = 0 (and L_b,c-1, or it would have filled in)
+        const bool use_b = two && has(b, cb);
         double v[4], vb[4], xv[4];
         if (b == c + 1) {
 #pragma unroll

@@ -1701,12 +1701,13 @@ __global__ void k_assemble(OptsDev o, DevPlan D, const double* __restrict__ Z, c
   if (w == 0 && idx < 4) sync[idx] = 0;
   if (idx >= total) return;
   const int r = (int)(idx / npad), c = (int)(idx % npad);
-  // systems on the tile dataflow read only the lower tiles inside the
-  // envelope of S (and the right-hand-side row): the other entries are not
-  // formed
+  // systems on the tile dataflow read only the lower tiles that are nonzero in
+  // the factor (and the right-hand-side row): the other entries are not formed
   if (npad > kCholSmallMaxNpad && r < npad) {
     const int ti = r / kCholNB, tj = c / kCholNB;
-    if (tj > ti || tj < D.chol_fc[W.fc_off + ti]) return;
+    const int nzw = (W.nblk + 31) / 32;
+    const int* nz = D.chol_tab + W.tab_off + 3 * W.nblk + 1;
+    if (tj > ti || !(((unsigned)nz[ti * nzw + (tj >> 5)] >> (tj & 31)) & 1u)) return;
   }
   const double* Hw = Hf + (size_t)W.f_base * 900;
   const double* gw = gf + (size_t)W.f_base * 30;

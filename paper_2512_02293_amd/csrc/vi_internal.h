@@ -75,7 +75,7 @@ struct WinDev {
   int flag_off, nflags;              // Cholesky tile flags [(nblk + 1) * nblk]
   int band;                          // tiles (i, j) with i - j > band are zero in S and in L
   int seg_base, nseg;                // segments of eliminated velocity / bias unknowns
-  int fc_off;                        // offset of the tile envelope (nblk + 1 entries) in chol_fc
+  int tab_off;                        // dataflow path: offset of its block-column table in chol_tab
   long long pix_base;                // global offset of the first keyframe's first pixel
   long long A_off, Linv_off, x_off;  // reduced system, diagonal-tile inverses, solution
   double* pose;
@@ -142,9 +142,9 @@ struct Plan {
   std::vector<int32_t> f_seg;                  // [F] segment that eliminates with the factor
   std::vector<int32_t> gram_map;               // (segment, first Gram tile) per workgroup of the segments' Grams
   int cond_len = 0;                            // keyframes of the longest segment
-  // per window, first nonzero tile column of every tile row of S and L (the
-  // right-hand-side row last, 0): tiles (i, j < fc[i]) are zero in both
-  std::vector<int32_t> chol_fc;
+  // per window of the dataflow path: chain order of the block columns, the ends
+  // and beginnings of the k-loops in it, bits of the nonzero tiles (build_plan)
+  std::vector<int32_t> chol_tab;
   int pdim = 15;                               // unknowns per keyframe: 15 (visual-inertial) or 7 (Sim(3) graph)
   int R = 0;                                   // relative-pose factors (pose-graph adjustment)
   std::vector<int32_t> rel_ii, rel_jj;         // global keyframe indices per factor
@@ -165,7 +165,7 @@ struct DevPlan {
   const int32_t *pair_off, *pair_z, *pair_zb;
   const int32_t* chol_tiles;
   const int32_t *rel_ii, *rel_jj, *rel_z, *rel_zb;
-  const int32_t *kf_off, *row_map, *chol_fc;
+  const int32_t *kf_off, *row_map, *chol_tab;
   const int32_t *kf_seg, *f_seg, *gram_map;
   const SegDev* segs;
   const WinDev* win;
