@@ -164,15 +164,12 @@ std::vector<int32_t> plan_signature(const std::vector<WinIn>& wins, bool use_imu
 }
 
 // ---------------------------------------------------------------------------
-// Order of the keyframes in a window's reduced system, and the envelope of S.
-// The Cholesky factor of S is nonzero only inside the envelope of S (in each
-// row, from the first nonzero column to the diagonal), so the tile dataflow
-// only visits tiles (i, j) with fc[i] <= j, and inside a tile only the
-// k >= max(fc[i], fc[j]).  Loop edges widen the envelope far beyond the band
-// of nearby keyframes; a reverse Cuthill-McKee order of the keyframe coupling
+// Order of the keyframes in a window's reduced system.  Elimination fills in
+// between the columns that a row couples with, so loop edges widen the band of
+// nearby keyframes far; a reverse Cuthill-McKee order of the keyframe coupling
 // graph (breadth-first from a pseudo-peripheral keyframe, neighbours by
-// increasing degree, the whole sequence reversed) narrows it again.  The
-// order is taken only when it lowers the factorisation's work.
+// increasing degree, the whole sequence reversed) narrows it again, and cutting
+// the sequence into independent parts lets their columns run side by side.
 // ---------------------------------------------------------------------------
 struct Coupling {
   int a, b;

@@ -134,10 +134,6 @@ __device__ __forceinline__ double seg_rhs(const DevPlan& D, const WinDev& W, con
   return v;
 }
 
-// LDS operations of one wave complete in order: a compiler barrier is enough
-// between a write of one lane and the read of another
-__device__ __forceinline__ void wave_lds_sync() { asm volatile("" ::: "memory"); }
-
 constexpr int kCondCols = 256;                         // columns (with the right-hand side) of a segment
 constexpr int kCondEv = 7;                             // columns that may touch every keyframe: right-hand side, global bias
 constexpr int kCondHx = 18 * 12;                       // per factor: V rows of both keyframes x their poses
@@ -156,36 +152,6 @@ __device__ __forceinline__ double cond_off(const OptsDev& o, const double* Hw, i
   const int r = e / 9, c = e % 9;
   if (!coord_active(o, i, 6 + r, N) || !coord_active(o, j, 6 + c, N)) return 0.0;
   return imu_hess<true>(Hw, N, i, 6 + r, j, 6 + c);
-}
-
-// Cholesky factor of a 9 x 9 SPD block by one wave, every lane in registers: L
-// holds the lower part packed by rows, on return the factor with 1 / L_jj in
-// rv.  Along with it each lane solves L x = v for its own v.  Returns the first
-// pivot that is not positive, or -1.
-__device__ __forceinline__ constexpr int tri9c(int i, int j) { return i * (i + 1) / 2 + j; }
-
-__device__ __forceinline__ int factor9_solve(double (&L)[46], double (&v)[9]) {
-  int bad = -1;
-#pragma unroll
-  for (int j = 0; j < 9; ++j) {
-    const double piv = L[tri9c(j, j)];
-    const bool ok = piv > 0.0;
-    if (!ok && bad < 0) bad = j;
-    const double r = ok ? rsqrt_refined(__builtin_fabs(piv)) : 1.0;
-    v[j] *= r;
-#pragma unroll
-    for (int i = 1; i < 9; ++i)
-      if (i > j) L[tri9c(i, j)] *= r;
-#pragma unroll
-    for (int i = 1; i < 9; ++i)
-#pragma unroll
-      for (int m = 1; m < 9; ++m)
-        if (i > j && m > j && m <= i) L[tri9c(i, m)] -= L[tri9c(i, j)] * L[tri9c(m, j)];
-#pragma unroll
-    for (int i = 1; i < 9; ++i)
-      if (i > j) v[i] -= L[tri9c(i, j)] * v[j];
-  }
-  return bad;
 }
 
 // The columns that tile t (16 of them) of a segment reaches: a pose column p is

@@ -12,18 +12,21 @@
 // One 256-thread workgroup solves one problem, every iteration in the same
 // launch, everything in LDS:
 //   * per factor (one lane each): residual and the 15 x 21 Jacobian with
-//     respect to (phi_x, phi_y, s, keyframe i, keyframe i+1), whitened by the
-//     inverse Cholesky factor of the factor covariance (so H = J^T J);
+//     respect to (phi_x, phi_y, s, keyframe i, keyframe i+1), then (one lane per
+//     column) whitened by the inverse Cholesky factor of the factor covariance
+//     (so H = J^T J);
 //   * the normal matrix is an arrowhead of 9 x 9 blocks: block-tridiagonal over
 //     the keyframes (a factor couples only i and i+1) with a 3-row border (the
 //     globals touch every factor); the damped blocks are assembled one entry per
 //     lane (15-term dot products in a fixed order);
 //   * block Cholesky along the keyframes (each step: the Schur update of the
 //     next diagonal and border blocks by the previous column, the 9 x 9 pivot
-//     factor in one lane's registers, the column solve), then the 3 x 3 border
-//     pivot, forward and back substitution.
-// The workgroup is latency-bound (about 3 barriers per keyframe per
-// iteration); problems of a batch run in parallel workgroups.
+//     factor with the column's rows solved along with it), then the 3 x 3 border
+//     pivot and the back substitution.
+// The workgroup is latency-bound, by the chain along the keyframes (20
+// keyframes, 10 iterations: 1680 us with three barriers and a one-lane factor
+// per keyframe, 1040 us with the chain on one wave and no barrier in it);
+// problems of a batch run in parallel workgroups.
 #include "vi_internal.h"
 #include "vi_math.h"
 
@@ -67,8 +70,8 @@ __device__ inline IILds carve(double* sh, int N) {
   return L;
 }
 
-// residual and whitened Jacobian of factor f -> L.r[15 f..], L.J[315 f..]; returns r^T Lambda r
-__device__ double linearize_factor(const IInitDesc& d, const IILds& L, int f, double G) {
+// residual and Jacobian of factor f -> L.r[15 f..], L.J[315 f..] (zero before)
+__device__ __forceinline__ void linearize_factor(const IInitDesc& d, const IILds& L, int f, double G) {
   const vi_preint* P = d.imu + f;
   const int i = f, j = f + 1;
   const double es = exp(L.s[0]);
@@ -120,7 +123,6 @@ __device__ double linearize_factor(const IInitDesc& d, const IILds& L, int f, do
   }
   for (int m = 0; m < 6; ++m) r[9 + m] = L.b[6 * j + m] - L.b[6 * i + m];
 
-  for (int e = 0; e < 15 * kJC; ++e) J[e] = 0.0;
   // d r_rot / d b_g,i = -Jr^-1(r_rot) Exp(r_rot)^T Jr(J_rot db_g) J_rot
   {
     double Jri[9], Er[9], Jw[9], T1[9], T2[9], T3[9];
@@ -156,31 +158,26 @@ __device__ double linearize_factor(const IInitDesc& d, const IILds& L, int f, do
     J[kJC * (9 + a) + 6 + a] = -1.0;
     J[kJC * (9 + a) + 15 + a] = 1.0;
   }
-  // whiten: rows 0..8 by L^-1 of the 9x9 covariance, rows 9..14 by 1/sqrt(cov_bias)
+}
+
+// whitens column c of factor f (c = kJC: the residual) in place: rows 0..8 by
+// L^-1 of the 9x9 covariance, rows 9..14 by 1/sqrt(cov_bias)
+__device__ __forceinline__ void whiten_column(const IInitDesc& d, const IILds& L, int f, int c) {
   const double* wf = d.wf + (size_t)kWF * f;
-  double Li[45];
-  for (int a = 0, e = 0; a < 9; ++a)
-    for (int c = 0; c <= a; ++c, ++e) Li[e] = wf[9 * a + c];
-  double cost = 0.0;
-  for (int c = 0; c <= kJC; ++c) {          // column kJC is the residual
-    double x[9], y[9];
-    for (int a = 0; a < 9; ++a) x[a] = c < kJC ? J[kJC * a + c] : r[a];
-    for (int a = 0, e = 0; a < 9; ++a) {
-      double s = 0.0;
-      for (int m = 0; m <= a; ++m, ++e) s += Li[e] * x[m];
-      y[a] = s;
-    }
-    for (int a = 0; a < 9; ++a) {
-      if (c < kJC) J[kJC * a + c] = y[a];
-      else r[a] = y[a];
-    }
-    for (int a = 9; a < 15; ++a) {
-      if (c < kJC) J[kJC * a + c] *= wf[81 + a - 9];
-      else r[a] *= wf[81 + a - 9];
-    }
+  double* p = c < kJC ? L.J + 15 * kJC * f + c : L.r + 15 * f;
+  const int st = c < kJC ? kJC : 1;
+  double x[9];
+#pragma unroll
+  for (int a = 0; a < 9; ++a) x[a] = p[st * a];
+#pragma unroll
+  for (int a = 0; a < 9; ++a) {
+    double s = 0.0;
+#pragma unroll
+    for (int m = 0; m <= a; ++m) s += wf[9 * a + m] * x[m];
+    p[st * a] = s;
   }
-  for (int a = 0; a < 15; ++a) cost += r[a] * r[a];
-  return cost;
+#pragma unroll
+  for (int a = 9; a < 15; ++a) p[st * a] *= wf[81 + a - 9];
 }
 
 // 15-term dot product of columns p and q of factor f's whitened Jacobian (q = kJC: the residual)
@@ -193,7 +190,7 @@ __device__ __forceinline__ double jdot(const IILds& L, int f, int p, int q) {
 }
 
 // in-place Cholesky (lower) of a 9x9 block in LDS, in one lane's registers; false if a pivot is not positive
-__device__ bool chol9(double* D) {
+__device__ __noinline__ bool chol9(double* D) {
   double a[81];
 #pragma unroll
   for (int e = 0; e < 81; ++e) a[e] = D[e];
@@ -273,7 +270,19 @@ __global__ void __launch_bounds__(kIIThreads) k_inertial_init(const IInitDesc* _
   double* xK = L.x + 3;                // [N][9] (v, b_g, b_a) per keyframe
   for (int it = 0; it <= iters; ++it) {
     // ---- residuals and whitened Jacobians
-    for (int f = t; f < F; f += kIIThreads) L.cf[f] = linearize_factor(d, L, f, G);
+    for (int e = t; e < 15 * kJC * F; e += kIIThreads) L.J[e] = 0.0;
+    __syncthreads();
+    for (int f = t; f < F; f += kIIThreads) linearize_factor(d, L, f, G);
+    __syncthreads();
+#pragma unroll 1
+    for (int e = t; e < (kJC + 1) * F; e += kIIThreads) whiten_column(d, L, e / (kJC + 1), e % (kJC + 1));
+    __syncthreads();
+    for (int f = t; f < F; f += kIIThreads) {
+      double c = 0.0;
+#pragma unroll
+      for (int a = 0; a < 15; ++a) c += L.r[15 * f + a] * L.r[15 * f + a];
+      L.cf[f] = c;
+    }
     __syncthreads();
     if (t == 0) {
       double c = 0.0;
@@ -322,87 +331,92 @@ __global__ void __launch_bounds__(kIIThreads) k_inertial_init(const IInitDesc* _
       }
     }
     __syncthreads();
-    // ---- block Cholesky along the keyframes with the border; forward substitution
-    for (int k = 0; k < N; ++k) {
-      if (k > 0) {
-        // Schur update by column k-1 (S_{k-1} = L_{k,k-1}, B_{k-1} = L_{G,k-1}, x_{k-1} = y_{k-1})
-        const double* Sp = L.S + 81 * (k - 1);
-        const double* Bp = L.B + 27 * (k - 1);
-        const double* yp = xK + 9 * (k - 1);
-        for (int e = t; e < 81 + 27 + 9 + 9 + 3; e += kIIThreads) {
-          if (e < 81) {
-            const int p = e / 9, q = e % 9;
-            double s = 0.0;
-            for (int m = 0; m < 9; ++m) s += Sp[9 * p + m] * Sp[9 * q + m];
-            L.D[81 * k + e] -= s;
-          } else if (e < 108) {
-            const int u = e - 81, p = u / 9, q = u % 9;
-            double s = 0.0;
-            for (int m = 0; m < 9; ++m) s += Bp[9 * p + m] * Sp[9 * q + m];
-            L.B[27 * k + u] -= s;
-          } else if (e < 117) {
-            const int p = e - 108;
-            double s = 0.0;
-            for (int m = 0; m < 9; ++m) s += Sp[9 * p + m] * yp[m];
-            xK[9 * k + p] -= s;
-          } else if (e < 126) {
-            const int u = e - 117, p = u / 3, q = u % 3;
-            double s = 0.0;
-            for (int m = 0; m < 9; ++m) s += Bp[9 * p + m] * Bp[9 * q + m];
-            L.C[u] -= s;
-          } else {
-            const int p = e - 126;
-            double s = 0.0;
-            for (int m = 0; m < 9; ++m) s += Bp[9 * p + m] * yp[m];
-            xG[p] -= s;
-          }
-        }
-        __syncthreads();
-      }
-      if (t == 0) {
+    // ---- block Cholesky along the keyframes with the border and the forward
+    // substitution, by one wave: every lane factors the 9x9 pivot in registers
+    // and carries a row of its own through it, lanes 0-8 S_k, 9-11 B_k, 12 the
+    // right-hand side, 16-24 the identity (L_kk^-1, kept in D_k for the
+    // substitution back)
+    if (t < 64) {
+      int er = 0;                        // entry (er, ec) of a packed 9x9 block
+      while ((er + 1) * (er + 2) / 2 <= t) ++er;
+      const int ec = t - er * (er + 1) / 2;
+      const int dr = min(er, 8), dc = min(ec, 8);
+      double vp[9];                      // this lane's row of the column before
+#pragma unroll
+      for (int q = 0; q < 9; ++q) vp[q] = 0.0;
+#pragma unroll 1
+      for (int k = 0; k < N; ++k) {
         double* Dk = L.D + 81 * k;
-        if (!chol9(Dk)) {
-          L.flag[0] = 3;
-        } else {
-          double* y = xK + 9 * k;
-          for (int a = 0; a < 9; ++a) {
-            double s = y[a];
-            for (int m = 0; m < a; ++m) s -= Dk[9 * a + m] * y[m];
-            y[a] = s / Dk[9 * a + a];
+        double* row = t < 9 ? L.S + 81 * min(k, F - 1) + 9 * t : (t < 12 ? L.B + 27 * k + 9 * (t - 9) : xK + 9 * k);
+        double v[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) v[q] = t < 13 ? row[q] : (t == 16 + q ? 1.0 : 0.0);
+        if (k > 0) {
+          // Schur update by column k-1 (S_{k-1} = L_{k,k-1}, B_{k-1} = L_{G,k-1}, x_{k-1} = y_{k-1})
+          const double* Sp = L.S + 81 * (k - 1);
+          double m = Dk[9 * dr + dc];
+#pragma unroll
+          for (int q = 0; q < 9; ++q) m -= Sp[9 * dr + q] * Sp[9 * dc + q];
+          if (t < 45) Dk[9 * dr + dc] = m;
+          const bool upd = t >= 9 && t < 13;
+#pragma unroll
+          for (int q = 0; q < 9; ++q) {
+            double u = 0.0;
+#pragma unroll
+            for (int m2 = 0; m2 < 9; ++m2) u += vp[m2] * Sp[9 * q + m2];
+            v[q] -= upd ? u : 0.0;
           }
+          wave_lds_sync();
         }
+        double a[46];
+#pragma unroll
+        for (int r = 0; r < 9; ++r)
+#pragma unroll
+          for (int q = 0; q <= r; ++q) a[tri9c(r, q)] = Dk[9 * r + q];
+        if (factor9_solve(a, v) >= 0) {
+          if (t == 0) L.flag[0] = 3;
+          break;
+        }
+        wave_lds_sync();
+        if (t < 13 && (t >= 9 || k < F)) {
+#pragma unroll
+          for (int q = 0; q < 9; ++q) row[q] = v[q];
+        }
+        if (t >= 16 && t < 25) {
+#pragma unroll
+          for (int q = 0; q < 9; ++q) Dk[9 * q + t - 16] = v[q];
+        }
+#pragma unroll
+        for (int q = 0; q < 9; ++q) vp[q] = v[q];
+        wave_lds_sync();
       }
-      __syncthreads();
-      if (L.flag[0]) break;
-      // column solve: rows of S_k and B_k times L_kk^-T
+      // the border's Schur complement: 9 entries of C, 3 of its right-hand side
       if (t < 12) {
-        const double* Dk = L.D + 81 * k;
-        double* row = t < 9 ? (k < F ? L.S + 81 * k + 9 * t : nullptr) : L.B + 27 * k + 9 * (t - 9);
-        if (row) {
-          for (int a = 0; a < 9; ++a) {
-            double s = row[a];
-            for (int m = 0; m < a; ++m) s -= row[m] * Dk[9 * a + m];
-            row[a] = s / Dk[9 * a + a];
+        const int p = t < 9 ? t / 3 : t - 9;
+        const double* b = t < 9 ? L.B + 9 * (t % 3) : xK;
+        const int st = t < 9 ? 27 : 9;
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+        for (int k = 0; k < N; ++k) {
+          const double* Bp = L.B + 27 * k + 9 * p;
+          const double* bk = b + st * k;
+#pragma unroll
+          for (int m = 0; m < 9; m += 3) {
+            s0 += Bp[m] * bk[m];
+            s1 += Bp[m + 1] * bk[m + 1];
+            s2 += Bp[m + 2] * bk[m + 2];
           }
         }
+        (t < 9 ? L.C + t : xG + t - 9)[0] -= s0 + s1 + s2;
       }
-      __syncthreads();
     }
+    __syncthreads();
     if (L.flag[0]) break;
-    // border: the last column's update, the 3x3 pivot, then back substitution
+    // border: the 3x3 pivot
     if (t == 0) {
-      const double* Bp = L.B + 27 * (N - 1);
-      const double* yp = xK + 9 * (N - 1);
       double C[9], y[3];
       for (int p = 0; p < 3; ++p) {
-        double s = xG[p];
-        for (int m = 0; m < 9; ++m) s -= Bp[9 * p + m] * yp[m];
-        y[p] = s;
-        for (int q = 0; q < 3; ++q) {
-          double c = L.C[3 * p + q];
-          for (int m = 0; m < 9; ++m) c -= Bp[9 * p + m] * Bp[9 * q + m];
-          C[3 * p + q] = c;
-        }
+        y[p] = xG[p];
+        for (int q = 0; q < 3; ++q) C[3 * p + q] = L.C[3 * p + q];
       }
       bool ok = true;
       for (int c = 0; c < 3; ++c) {
@@ -430,24 +444,35 @@ __global__ void __launch_bounds__(kIIThreads) k_inertial_init(const IInitDesc* _
           y[a] = s / C[3 * a + a];
         }
         for (int a = 0; a < 3; ++a) xG[a] = y[a];
-        // x_k = L_kk^-T (y_k - L_{k+1,k}^T x_{k+1} - L_{G,k}^T x_G), k = N-1 .. 0
-        for (int k = N - 1; k >= 0; --k) {
-          const double* Dk = L.D + 81 * k;
-          double z[9];
-          for (int m = 0; m < 9; ++m) {
-            double s = xK[9 * k + m];
-            if (k < F)
-              for (int p = 0; p < 9; ++p) s -= L.S[81 * k + 9 * p + m] * xK[9 * (k + 1) + p];
-            for (int p = 0; p < 3; ++p) s -= L.B[27 * k + 9 * p + m] * xG[p];
-            z[m] = s;
-          }
-          for (int a = 8; a >= 0; --a) {
-            double s = z[a];
-            for (int m = a + 1; m < 9; ++m) s -= Dk[9 * m + a] * z[m];
-            z[a] = s / Dk[9 * a + a];
-          }
-          for (int m = 0; m < 9; ++m) xK[9 * k + m] = z[m];
+      }
+    }
+    __syncthreads();
+    if (L.flag[0]) break;
+    // back substitution x_k = L_kk^-T (y_k - L_{G,k}^T x_G - L_{k+1,k}^T x_{k+1}):
+    // the border's part for all k at once, the chain by one wave
+    for (int e = t; e < 9 * N; e += kIIThreads) {
+      const double* Bk = L.B + 27 * (e / 9) + e % 9;
+      xK[e] -= Bk[0] * xG[0] + Bk[9] * xG[1] + Bk[18] * xG[2];
+    }
+    __syncthreads();
+    if (t < 64) {
+      const int q = min(t, 8);
+#pragma unroll 1
+      for (int k = N - 1; k >= 0; --k) {
+        if (k < F) {
+          double s = xK[9 * k + q];
+#pragma unroll
+          for (int p = 0; p < 9; ++p) s -= L.S[81 * k + 9 * p + q] * xK[9 * (k + 1) + p];
+          wave_lds_sync();
+          if (t < 9) xK[9 * k + q] = s;
+          wave_lds_sync();
         }
+        double s = 0.0;
+#pragma unroll
+        for (int p = 0; p < 9; ++p) s += L.D[81 * k + 9 * p + q] * xK[9 * k + p];
+        wave_lds_sync();
+        if (t < 9) xK[9 * k + q] = s;
+        wave_lds_sync();
       }
     }
     __syncthreads();

@@ -1,7 +1,7 @@
 // Device-side FP64 helpers for the visual-inertial step: 3x3 algebra, the
 // rotation exponential/logarithm and right Jacobians, and quaternions.
 // Matrices are row-major double[9].  All functions are written for single
-// lanes; no cross-lane communication happens here.
+// lanes, without cross-lane communication, except the last ones, of one wave.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -218,6 +218,40 @@ __device__ inline void quat_retract(double* q, const double* w) {
   double nw = aw * bw - ax * bx - ay * by - az * bz;
   const double inv = 1.0 / sqrt(nx * nx + ny * ny + nz * nz + nw * nw);
   q[0] = nx * inv; q[1] = ny * inv; q[2] = nz * inv; q[3] = nw * inv;
+}
+
+// LDS operations of one wave complete in order: a compiler barrier is enough
+// between a write of one lane and the read of another
+__device__ __forceinline__ void wave_lds_sync() { asm volatile("" ::: "memory"); }
+
+// Cholesky factor of a 9 x 9 SPD block by one wave, every lane in registers: L
+// holds the lower part packed by rows, on return the factor with 1 / L_jj in
+// rv.  Along with it each lane solves L x = v for its own v.  Returns the first
+// pivot that is not positive, or -1.
+__device__ __forceinline__ constexpr int tri9c(int i, int j) { return i * (i + 1) / 2 + j; }
+
+__device__ __forceinline__ int factor9_solve(double (&L)[46], double (&v)[9]) {
+  int bad = -1;
+#pragma unroll
+  for (int j = 0; j < 9; ++j) {
+    const double piv = L[tri9c(j, j)];
+    const bool ok = piv > 0.0;
+    if (!ok && bad < 0) bad = j;
+    const double r = ok ? rsqrt_refined(__builtin_fabs(piv)) : 1.0;
+    v[j] *= r;
+#pragma unroll
+    for (int i = 1; i < 9; ++i)
+      if (i > j) L[tri9c(i, j)] *= r;
+#pragma unroll
+    for (int i = 1; i < 9; ++i)
+#pragma unroll
+      for (int m = 1; m < 9; ++m)
+        if (i > j && m > j && m <= i) L[tri9c(i, m)] -= L[tri9c(i, j)] * L[tri9c(m, j)];
+#pragma unroll
+    for (int i = 1; i < 9; ++i)
+      if (i > j) v[i] -= L[tri9c(i, j)] * v[j];
+  }
+  return bad;
 }
 
 }  // namespace vi
