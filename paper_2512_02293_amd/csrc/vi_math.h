@@ -72,13 +72,43 @@ __device__ __forceinline__ void skew(const double* w, double* S) {
   S[6] = -w[1]; S[7] = w[0];  S[8] = 0.0;
 }
 
+// Functions of the angle t = |w| by their power series in t^2.  Up to t^2 =
+// kSeriesT2 (t = 0.5, where an increment, a residual or the rotation of one IMU
+// sample lies) the dropped terms are below 2^-54 of the sum, without the
+// cancellation of 1 - cos t and t - sin t, and 7 or 8 fused operations replace
+// a square root, a sine, a cosine and divisions (some 200 instructions on the
+// serial lanes that form the inertial factors).
+constexpr double kSeriesT2 = 0.25;
+__device__ __forceinline__ double series_sinc(double x) {           // sin t / t
+  return 1.0 + x * (-1.0 / 6 + x * (1.0 / 120 + x * (-1.0 / 5040 + x * (1.0 / 362880 + x * (-1.0 / 39916800 +
+         x * (1.0 / 6227020800.0))))));
+}
+__device__ __forceinline__ double series_cosc(double x) {           // (1 - cos t) / t^2
+  return 0.5 + x * (-1.0 / 24 + x * (1.0 / 720 + x * (-1.0 / 40320 + x * (1.0 / 3628800 + x * (-1.0 / 479001600 +
+         x * (1.0 / 87178291200.0))))));
+}
+__device__ __forceinline__ double series_sinc3(double x) {          // (t - sin t) / t^3
+  return 1.0 / 6 + x * (-1.0 / 120 + x * (1.0 / 5040 + x * (-1.0 / 362880 + x * (1.0 / 39916800 + x * (-1.0 / 6227020800.0 +
+         x * (1.0 / 1307674368000.0))))));
+}
+// (1 - t / 2 cot(t / 2)) / t^2 = sum |B_2n| t^(2n - 2) / (2n)!
+__device__ __forceinline__ double series_cot(double x) {
+  return 1.0 / 12 + x * (1.0 / 720 + x * (1.0 / 30240 + x * (1.0 / 1209600 + x * (1.0 / 47900160 +
+         x * (691.0 / 1307674368000.0 + x * (1.0 / 74724249600.0 + x * (3617.0 / 10670622842880000.0)))))));
+}
+// asin(s) / s, x = s^2 up to 1 / 64
+__device__ __forceinline__ double series_asinc(double x) {
+  return 1.0 + x * (1.0 / 6 + x * (3.0 / 40 + x * (5.0 / 112 + x * (35.0 / 1152 + x * (63.0 / 2816 + x * (231.0 / 13312 +
+         x * (143.0 / 10240 + x * (6435.0 / 557056))))))));
+}
+
 // Exp(w) by Rodrigues: I + a K + b K^2 with K = [w]x, a = sin t / t, b = (1 - cos t) / t^2.
 __device__ inline void so3_exp(const double* w, double* R) {
   const double t2 = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
   double a, b;
-  if (t2 < 1e-16) {
-    a = 1.0 - t2 / 6.0;
-    b = 0.5 - t2 / 24.0;
+  if (t2 < kSeriesT2) {
+    a = series_sinc(t2);
+    b = series_cosc(t2);
   } else {
     const double t = sqrt(t2);
     a = sin(t) / t;
@@ -95,14 +125,14 @@ __device__ inline void so3_exp(const double* w, double* R) {
 // comes from the symmetric part.
 __device__ inline void so3_log(const double* R, double* w) {
   const double vx = R[7] - R[5], vy = R[2] - R[6], vz = R[3] - R[1];
-  const double s = 0.5 * sqrt(vx * vx + vy * vy + vz * vz);
+  const double s2 = 0.25 * (vx * vx + vy * vy + vz * vz);
   const double c = 0.5 * (R[0] + R[4] + R[8] - 1.0);
-  const double t = atan2(s, c);
-  if (t < 1e-6) {
-    const double f = 0.5 * (1.0 + t * t / 6.0);
+  if (s2 < 1.0 / 64 && c > 0.0) {
+    const double f = 0.5 * series_asinc(s2);     // t / (2 sin t)
     w[0] = f * vx; w[1] = f * vy; w[2] = f * vz;
     return;
   }
+  const double t = atan2(sqrt(s2), c);
   if (M_PI - t > 1e-6) {
     const double f = 0.5 * t / sin(t);
     w[0] = f * vx; w[1] = f * vy; w[2] = f * vz;
@@ -132,9 +162,9 @@ __device__ inline void so3_log(const double* R, double* w) {
 __device__ inline void so3_jr(const double* w, double* J) {
   const double t2 = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
   double a, b;
-  if (t2 < 1e-12) {
-    a = 0.5 - t2 / 24.0;
-    b = 1.0 / 6.0 - t2 / 120.0;
+  if (t2 < kSeriesT2) {
+    a = series_cosc(t2);
+    b = series_sinc3(t2);
   } else {
     const double t = sqrt(t2);
     a = (1.0 - cos(t)) / t2;
@@ -150,8 +180,8 @@ __device__ inline void so3_jr(const double* w, double* J) {
 __device__ inline void so3_jr_inv(const double* w, double* J) {
   const double t2 = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
   double c;
-  if (t2 < 1e-12) {
-    c = 1.0 / 12.0 + t2 / 720.0;
+  if (t2 < kSeriesT2) {
+    c = series_cot(t2);
   } else {
     const double t = sqrt(t2);
     c = 1.0 / t2 - (1.0 + cos(t)) / (2.0 * t * sin(t));
@@ -202,9 +232,10 @@ __device__ inline void rot_to_quat(const double* R, double* q) {
 __device__ inline void quat_retract(double* q, const double* w) {
   const double t2 = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
   double sh, ch;
-  if (t2 < 1e-16) {
-    sh = 0.5 - t2 / 48.0;      // sin(t/2)/t
-    ch = 1.0 - t2 / 8.0;       // cos(t/2)
+  if (t2 < kSeriesT2) {
+    const double x = 0.25 * t2;
+    sh = 0.5 * series_sinc(x);         // sin(t/2)/t
+    ch = 1.0 - x * series_cosc(x);     // cos(t/2)
   } else {
     const double t = sqrt(t2);
     sh = sin(0.5 * t) / t;
