@@ -190,7 +190,7 @@ __device__ __forceinline__ double jdot(const IILds& L, int f, int p, int q) {
 }
 
 // in-place Cholesky (lower) of a 9x9 block in LDS, in one lane's registers; false if a pivot is not positive
-__device__ __noinline__ bool chol9(double* D) {
+__device__ bool chol9(double* D) {
   double a[81];
 #pragma unroll
   for (int e = 0; e < 81; ++e) a[e] = D[e];
@@ -274,7 +274,6 @@ __global__ void __launch_bounds__(kIIThreads) k_inertial_init(const IInitDesc* _
     __syncthreads();
     for (int f = t; f < F; f += kIIThreads) linearize_factor(d, L, f, G);
     __syncthreads();
-#pragma unroll 1
     for (int e = t; e < (kJC + 1) * F; e += kIIThreads) whiten_column(d, L, e / (kJC + 1), e % (kJC + 1));
     __syncthreads();
     for (int f = t; f < F; f += kIIThreads) {
@@ -344,7 +343,6 @@ __global__ void __launch_bounds__(kIIThreads) k_inertial_init(const IInitDesc* _
       double vp[9];                      // this lane's row of the column before
 #pragma unroll
       for (int q = 0; q < 9; ++q) vp[q] = 0.0;
-#pragma unroll 1
       for (int k = 0; k < N; ++k) {
         double* Dk = L.D + 81 * k;
         double* row = t < 9 ? L.S + 81 * min(k, F - 1) + 9 * t : (t < 12 ? L.B + 27 * k + 9 * (t - 9) : xK + 9 * k);
@@ -457,7 +455,6 @@ __global__ void __launch_bounds__(kIIThreads) k_inertial_init(const IInitDesc* _
     __syncthreads();
     if (t < 64) {
       const int q = min(t, 8);
-#pragma unroll 1
       for (int k = N - 1; k >= 0; --k) {
         if (k < F) {
           double s = xK[9 * k + q];
