@@ -503,9 +503,11 @@ __global__ void __launch_bounds__(256) k_backsub_pg(double z_min, double d_min, 
   for (int i = tid; i < 12 * k; i += 256) rel_s[i] = (R)rel[(size_t)D.src_edges[e0 + i / 12] * 12 + i % 12];
   if (tid < k) {
     const int e = D.src_edges[e0 + tid];
-    const int lj = D.jj[e] - W.kf_base;
     double Mi[42], Mj[42];
-    pg_maps(rel + (size_t)e * 12, Rw + (size_t)D.jj[e] * 9, W.scale[ls] / W.scale[lj], Mi, Mj);
+    // s_i / s_j from the edge's s_i / s_j R_ji: the scales themselves are being
+    // retracted by the workgroups above in this same launch
+    const double* r = rel + (size_t)e * 12;
+    pg_maps(r, Rw + (size_t)D.jj[e] * 9, sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]), Mi, Mj);
     const double* xi = xw + D.kf_off[src];
     const double* xj = xw + D.kf_off[D.jj[e]];
     for (int c = 0; c < 6; ++c) {
