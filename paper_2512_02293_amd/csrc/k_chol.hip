@@ -72,7 +72,7 @@ __device__ __forceinline__ bool spin_flag(const int* f, int* sync, bool near) {
     if ((++spins & 31) == 0) {
       if (__builtin_amdgcn_readfirstlane(load_flag(sync + 1)) != 0) return false;
       if (spins > kSpinLimit) {
-        if (threadIdx.x == 0) __hip_atomic_store(sync + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((threadIdx.x & 63) == 0) __hip_atomic_store(sync + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return false;
       }
     }
@@ -998,7 +998,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_chol_small(DevPlan D, double*
 // (tile (b, c) read before its x_b is waited for); then x_c = L_cc^-T t_c is
 // written and published.  After an aborted factorisation (or a wait past its
 // bound) the window is marked failed and the waits stop; every wave runs the
-// same barriers either way.
+// same barriers either way.  The waves wait each for itself, so whether any of
+// them gave up is decided by the workgroup before it publishes.
 __global__ void __launch_bounds__(256) k_chol_bs(DevPlan D, int t0, int nbs, const double* __restrict__ Aall,
                                                  const double* __restrict__ Linvall, double* __restrict__ xall,
                                                  int* __restrict__ flagsall, int* __restrict__ sync,
@@ -1007,9 +1008,13 @@ __global__ void __launch_bounds__(256) k_chol_bs(DevPlan D, int t0, int nbs, con
   __shared__ double tv[NB];
   __shared__ double xa[NB];
   __shared__ int tk;
+  __shared__ int gave_up;    // a wave's sums are incomplete
   const int tid = threadIdx.x, q = tid & 31, r8 = tid >> 5, lane = tid & 63;
   while (true) {
-    if (tid == 0) tk = atomicAdd(sync + 2, 1);
+    if (tid == 0) {
+      tk = atomicAdd(sync + 2, 1);
+      gave_up = 0;
+    }
     __syncthreads();
     const int t = tk;
     __syncthreads();
@@ -1103,6 +1108,7 @@ __global__ void __launch_bounds__(256) k_chol_bs(DevPlan D, int t0, int nbs, con
     }
     part[0][r8][q] = acc;
     part[1][r8][q] = accb;
+    if (aborted && lane == 0) gave_up = 1;
     __syncthreads();
     if (tid < NB) {
       double s = A[(size_t)npad * npad + NB * c + q];
@@ -1138,7 +1144,7 @@ __global__ void __launch_bounds__(256) k_chol_bs(DevPlan D, int t0, int nbs, con
         for (int r = 0; r < NB; ++r) s += lbb[r] * tv[r];
         x[NB * cb + q] = (NB * cb + q < W.n) ? s : 0.0;
       }
-      if (aborted) {
+      if (gave_up) {
         if (lane == 0) set_status(stall + w, VI_EDEVICE, -1);
       } else {
         // both blocks published by one release
