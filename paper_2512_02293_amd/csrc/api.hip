@@ -835,11 +835,29 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
 // keyframe * unknowns-per-keyframe + unknown
 int natural_coord(const Plan& P, int w, int c) {
   const WinDev& W = P.win[w];
-  if (c >= kNaturalDetail) return c - kNaturalDetail;
   if (c < 0 || c >= W.n) return c;
   int32_t m = P.row_map[(size_t)W.x_off + c];
   while (m < 0 && c > 0) m = P.row_map[(size_t)W.x_off + --c];   // a row between two parts: the one before it
   return (m >> 8) * P.pdim + (m & 255);
+}
+
+// Error of window w from its status word: code, and the coordinate or other
+// detail.  An entry of the eliminated unknowns is reported ahead of what it
+// spoils in the reduced system, behind the checks of the inputs (details below
+// 0); a pivot of theirs like one of the reduced system, the smaller coordinate
+// of both.
+void window_error(const Plan& P, int w, const DevStatus& st, int* code, int* detail) {
+  *code = st.code;
+  *detail = st.code == VI_ENOTPD ? natural_coord(P, w, st.detail) : st.detail;
+  if (st.elim == 0 || st.code == VI_EDEVICE || (st.code != 0 && st.detail < 0)) return;
+  const int coord = kElimPivot - 1 - (st.elim & (kElimPivot - 1));
+  if (st.elim >= kElimNonfinite) {
+    *code = VI_ENONFINITE;
+    *detail = coord;
+  } else if (st.code == 0 || (st.code == VI_ENOTPD && coord < *detail)) {
+    *code = VI_ENOTPD;
+    *detail = coord;
+  }
 }
 
 void set_range(Plan& P, int range) {
@@ -1293,7 +1311,7 @@ vi_status run(vi_ctx* ctx, const std::vector<WinIn>& wins, const vi_opts* o, int
   HIPCHK(ctx, hipStreamSynchronize(sp));
   int first_bad = -1;
   for (int wi = 0; wi < P.n_win; ++wi) {
-    if (hs[wi].code != 0 && first_bad < 0) first_bad = wi;
+    if ((hs[wi].code != 0 || hs[wi].elim != 0) && first_bad < 0) first_bad = wi;
     vi_report* rep = wins[wi].rep;
     if (!rep) continue;
     const double* tr = trace.data() + (size_t)wi * kTraceLen;
@@ -1320,14 +1338,16 @@ vi_status run(vi_ctx* ctx, const std::vector<WinIn>& wins, const vi_opts* o, int
     for (int wi = 0; wi < P.n_win; ++wi)
       accepted[wi] = wtrace[(size_t)wi * kTraceLen + 2] < wtrace[(size_t)wi * kTraceLen] ? 1 : 0;
   if (first_bad >= 0) {
-    const DevStatus& b = hs[first_bad];
-    if (b.code == VI_ENOTPD)
+    const int step = hs[first_bad].iters;
+    int code, detail;
+    window_error(P, first_bad, hs[first_bad], &code, &detail);
+    if (code == VI_ENOTPD)
       return fail(ctx, VI_ENOTPD, "window %d: reduced system not positive definite at coordinate %d (step %d)",
-                  first_bad, natural_coord(P, first_bad, b.detail), b.iters);
-    if (b.code == VI_ENONFINITE)
+                  first_bad, detail, step);
+    if (code == VI_ENONFINITE)
       return fail(ctx, VI_ENONFINITE, "window %d: non-finite reduced system at coordinate %d (step %d)", first_bad,
-                  b.detail, b.iters);
-    return fail(ctx, (vi_status)b.code, "window %d: device error %d (detail %d)", first_bad, b.code, b.detail);
+                  detail, step);
+    return fail(ctx, (vi_status)code, "window %d: device error %d (detail %d)", first_bad, code, detail);
   }
   ctx->err.clear();
   return VI_OK;

@@ -189,7 +189,10 @@ __device__ __forceinline__ void cond_segment(const OptsDev& o, const SegDev& S, 
   double* ev = Bw + 81 * (len + 1);                    // [len][9][7]
   double* sv = ev + kCondNV * kCondEv * len;           // [2][9][9]      V of a against a - 1, of b against b + 1
   double* Hx = sv + 162;                               // [k1 - k0][18][12], factor k0 + f: (V_f, V_f+1) x (pose_f, pose_f+1)
-  bool finite = true;
+  int wrong = 0;                                       // what this thread finds (DevStatus::elim)
+  auto check = [&](bool ok, int kind, int kf, int v) {   // unknown v of keyframe kf's V
+    if (!ok) wrong = max(wrong, kind + kElimPivot - 1 - (15 * kf + 6 + v));
+  };
   // unknowns 0..nv-1 of every keyframe of the segment are solved (the biases
   // may be held, or be the shared one of the last keyframe, never in a segment);
   // the rows and columns of the others are those of the identity
@@ -222,13 +225,14 @@ __device__ __forceinline__ void cond_segment(const OptsDev& o, const SegDev& S, 
         double m = (i > 0 ? dn[0] : 0.0) + (i < N - 1 ? dn[1] : 0.0), v[9];
         if (er == ec) m += o.lambda * m;
         if (er >= nv) m = er == ec ? 1.0 : 0.0;
-        finite = finite && (lane >= 45 || isfinite(m));
+        bool finite = lane >= 45 || isfinite(m);
         // lanes 0-8: their row of the next coupling; lanes 16-24: of the identity
 #pragma unroll
         for (int q = 0; q < 9; ++q) {
           v[q] = (lane < nv && q < nv && !part) ? kn[q] : (lane == 16 + q ? 1.0 : 0.0);
           finite = finite && isfinite(v[q]);
         }
+        check(finite, kElimNonfinite, i, dr);
         if (i + dir != end) fetch(i + dir);
         // minus the neighbours' terms: the one before in the chain, both at the middle
 #pragma unroll 1
@@ -248,7 +252,7 @@ __device__ __forceinline__ void cond_segment(const OptsDev& o, const SegDev& S, 
           L[2 * q + 1] = x[1];
         }
         const int bad = factor9_solve(L, v);
-        if (bad >= 0 && lane == 0 && st) set_status(st, VI_ENOTPD, kNaturalDetail + 15 * i + 6 + bad);
+        check(bad < 0, kElimPivot, i, bad);
         // B of the next keyframe (the middle keeps its right one apart)
         if (lane < 9 && !part) {
           double* B = Bw + 81 * (i + dir == mid && dir < 0 ? len : i + dir - a) + 9 * lane;
@@ -268,14 +272,14 @@ __device__ __forceinline__ void cond_segment(const OptsDev& o, const SegDev& S, 
       if (t < 162) {
         const int e = t % 81, i = t < 81 ? a : b, j = t < 81 ? a - 1 : b + 1;
         const double v = (j >= 0 && j < N) ? cond_off(o, Hw, N, i, j, e) : 0.0;
-        finite = finite && isfinite(v);
+        check(isfinite(v), kElimNonfinite, i, e / 9);
         sv[t] = v;
       }
 #pragma unroll 1
       for (int e = t; e < kCondNV * len; e += 384) {
         const int i = a + e / kCondNV, r = e % kCondNV;
         const double v = r < nv ? imu_grad<true>(gw, N, i, 6 + r) : 0.0;
-        finite = finite && isfinite(v);
+        check(isfinite(v), kElimNonfinite, i, r);
         ev[kCondEv * e] = v;
         if (S.gb >= 0) {
           // the shared bias: the entries against the biases of i - 1, i, i + 1
@@ -284,7 +288,7 @@ __device__ __forceinline__ void cond_segment(const OptsDev& o, const SegDev& S, 
             double u = 0.0;
             if (r < nv)
               for (int b2 = max(i - 1, 0); b2 <= min(i + 1, N - 1); ++b2) u += imu_hess<true>(Hw, N, i, 6 + r, b2, 9 + q);
-            finite = finite && isfinite(u);
+            check(isfinite(u), kElimNonfinite, i, r);
             ev[kCondEv * e + 1 + q] = u;
           }
         }
@@ -295,17 +299,13 @@ __device__ __forceinline__ void cond_segment(const OptsDev& o, const SegDev& S, 
         const int i = f + r / 9;
         const double h = agent_load<true>(Hw + (size_t)f * 900 + (15 * (r / 9) + 6 + r % 9) * 30 + 15 * (c / 6) + c % 6);
         const double v = (i >= a && i <= b && r % 9 < nv && f + c / 6 >= o.n_fixed) ? h : 0.0;
-        finite = finite && isfinite(v);
+        check(isfinite(v), kElimNonfinite, i, r % 9);
         Hx[e] = v;
       }
     }
     __syncthreads();
   }
-  // a non-finite entry outranks the pivot that it spoils
-  if (!finite && st) {
-    const bool set = atomicCAS(&st->code, VI_ENOTPD, VI_ENONFINITE) == VI_ENOTPD || atomicCAS(&st->code, 0, VI_ENONFINITE) == 0;
-    if (set) st->detail = 15 * a + 6;
-  }
+  if (wrong && st) atomicMax(&st->elim, wrong);
   // Y by tiles of 16 columns: along each side T = C_i - B_i Y_prev,
   // Y_i = L_i^-1 T, then the middle with both sides' terms
   double* Y = cond + S.y_off;

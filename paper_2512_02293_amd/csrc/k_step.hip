@@ -31,6 +31,8 @@ __device__ __forceinline__ void set_status(DevStatus* st, int code, int detail) 
   if (atomicCAS(&st->code, 0, code) == 0) st->detail = detail;
 }
 
+__device__ __forceinline__ bool takes_step(const DevStatus& st) { return st.code == 0 && st.elim == 0 && st.conv == 0; }
+
 // ---------------------------------------------------------------------------
 // wave-wide reduce-scatter of 32 doubles: afterwards lane l holds the sum over
 // the 64 lanes of element (l >> 1).  32 exchanges instead of 32 * 6.
@@ -172,7 +174,7 @@ __device__ __forceinline__ float reduce16(float (&v)[16], int lane) {
 
 }  // namespace
 }  // namespace vi
-#include "k_cond.h"   // uses set_status and reduce16
+#include "k_cond.h"   // uses reduce16
 namespace vi {
 namespace {
 
@@ -1392,7 +1394,11 @@ __global__ void __launch_bounds__(kLocalThreads) k_local(int N, int nkr_max, int
     if (threadIdx.x == 0 && st && tol > 0.0 && slot > 0) {
       const double prev = trace[(size_t)w * kTraceLen + 2 * (slot - 1)];
       const double cur = trace[(size_t)w * kTraceLen + 2 * slot];
-      if (!(prev - cur > tol * prev)) st[w].conv = 1;
+      if (!(prev - cur > tol * prev)) {
+        st[w].conv = 1;
+        // a step not taken needs no pivots (one that failed before keeps its own)
+        if (st[w].elim < kElimNonfinite && st[w].iters == slot) st[w].elim = 0;
+      }
     }
     return;
   }
@@ -1809,13 +1815,13 @@ __global__ void __launch_bounds__(256, 5) k_backsub_retract(OptsDev o, int N, De
     if (blockIdx.x != 0) return;
     const SegDev& S = D.segs[blockIdx.y];
     const WinDev& W = D.win[S.w];
-    if (st[S.w].code == 0 && st[S.w].conv == 0) cond_backsub(o, D, S, W, cond, x + W.x_off, seg_lds);
+    if (takes_step(st[S.w])) cond_backsub(o, D, S, W, cond, x + W.x_off, seg_lds);
     return;
   }
   const int src = (int)blockIdx.y - nseg;
   if (src >= N) {
     const int w = src - N;
-    if (blockIdx.x != 0 || st[w].code != 0 || st[w].conv != 0) return;
+    if (blockIdx.x != 0 || !takes_step(st[w])) return;
     const WinDev& W = D.win[w];
     const double* xw = x + W.x_off;
     // one bias for the window: its increment (the last keyframe's slot) moves every keyframe's
@@ -1848,7 +1854,7 @@ __global__ void __launch_bounds__(256, 5) k_backsub_retract(OptsDev o, int N, De
   const int w = D.win_of_kf[src];
   const WinDev W = D.win[w];
   const int HW = W.HW;
-  if (st[w].code != 0 || st[w].conv != 0 || (int)blockIdx.x * 256 * ppt >= HW) return;
+  if (!takes_step(st[w]) || (int)blockIdx.x * 256 * ppt >= HW) return;
   const int ls = src - W.kf_base;
   const int e0 = D.src_off[src];
   const int k = D.src_off[src + 1] - e0;
@@ -1927,7 +1933,7 @@ __global__ void __launch_bounds__(256, 5) k_backsub_retract(OptsDev o, int N, De
 __global__ void k_reset_status(DevStatus* st, int n, int* cnt, int ncnt) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < ncnt) cnt[i] = 0;
-  if (i < n) { st[i].code = 0; st[i].detail = 0; st[i].iters = 0; st[i].conv = 0; }
+  if (i < n) { st[i].code = 0; st[i].detail = 0; st[i].iters = 0; st[i].conv = 0; st[i].elim = 0; }
 }
 
 // ---------------------------------------------------------------------------

@@ -49,17 +49,21 @@ constexpr int kTraceLen = 2 * (kMaxIters + 1);
 constexpr int kCondSpan = 12;
 constexpr int kCondMinLen = 3;
 constexpr int kCondNV = 9;
-// status details of at least this hold keyframe * 15 + unknown of the window
-// (a pivot of the eliminated unknowns), not a coordinate of the reduced system
-constexpr int kNaturalDetail = 1 << 24;
-
 // Device status word of one window: first error (vi_status), its detail (e.g.
-// pivot index), and the number of committed steps.
+// pivot index), the number of committed steps, whether the tolerance stopped it,
+// and what the elimination of velocities and biases found (elim).  That runs
+// beside the vision assembly, ahead of the checks whose place its own have in
+// the order of errors (a non-finite entry with the assembly's, a pivot with the
+// factorisation's), so it is kept apart: kElimNonfinite or kElimPivot, plus
+// kElimPivot - 1 minus the coordinate (keyframe * 15 + unknown), the largest
+// kept; 0: nothing.
+constexpr int kElimPivot = 1 << 20, kElimNonfinite = 1 << 21;
 struct DevStatus {
   int code;
   int detail;
   int iters;
-  int conv;          // 1 once the tolerance stop has frozen the window
+  int conv;      // tolerance stop reached: the window takes no further step
+  int elim;
 };
 
 // Per-window device descriptor.
