@@ -458,7 +458,7 @@ __global__ void k_assemble_pg(int n_fixed, double lambda, DevPlan D, const doubl
       const int p0 = poff[b * N + b], p1 = poff[b * N + b + 1];
       for (int it = p0; it < p1; ++it) val += ZV[D.pair_zb[it] + cb];
     }
-    if (!isfinite(val)) set_status_pg(st + w, VI_ENONFINITE, n + 7 * b + cb);
+    if (!isfinite(val)) set_status_pg(st + w, VI_ENONFINITE, 7 * (N + b) + cb);   // (behind the matrix's coordinates)
   }
   A[W.A_off + idx] = val;
 }

@@ -1784,7 +1784,7 @@ __global__ void k_assemble(OptsDev o, DevPlan D, const double* __restrict__ Z, c
       if (o.use_imu)
         val += imu_grad_folded(gw, N, b, cb, o.bias_global != 0) - seg_rhs(D, W, cond, b, cb, o.bias_global != 0);
     }
-    if (!isfinite(val)) set_status(st + w, VI_ENONFINITE, n + 15 * b + cb);
+    if (!isfinite(val)) set_status(st + w, VI_ENONFINITE, 15 * (N + b) + cb);   // (behind the matrix's coordinates)
   }
   A[W.A_off + idx] = val;
 }
