@@ -244,56 +244,77 @@ std::vector<int> rcm_order(int N, const std::vector<std::vector<int>>& adj) {
 // Nested dissection of a sequence of keyframes along its order: the first part
 // L, the rest R without the keyframes T next to L, and T; L and R (from its far
 // end towards T) are independent of each other, so the factorisation runs
-// through both at once, and T comes last.  levels > 1: L and R again.  Appends
-// to out, -1 where the next keyframe has to start a tile of its own (with a
-// tile shared between two parts the second would wait for the first).
+// through both at once, and T comes last.  levels > 1: L and R again.
 constexpr int kCutLevels = 3;                            // at most 8 independent parts (4: 474 instead of 445 us below)
 constexpr int kCutPad = ((1 << kCutLevels) - 1) * (kCholNB - 1);   // rows that they may skip
 
-void dissect(const std::vector<int>& seq, int levels, const std::vector<int>& dim,
-             const std::vector<std::vector<int>>& adj, std::vector<char>& mark, std::vector<int>& out) {
+struct Parts {
+  std::vector<int> seq, T;
+  std::vector<Parts> sides;  // L and R, or none: not cut
+};
+
+// pos: -1 for every keyframe, here and on return
+void dissect(Parts& P, int levels, const std::vector<int>& dim, const std::vector<std::vector<int>>& adj,
+             std::vector<int>& pos) {
+  const std::vector<int>& seq = P.seq;
   const int n = (int)seq.size();
-  int cut = -1, best = 0;
-  for (int a : seq) best += dim[a];
-  const int all = best;
-  if (levels > 0) {
-    // cuts at every 32nd of the sequence: the longest chain L or R, then T
-    for (int q = 4; q <= 28; ++q) {
-      const int m = (int)((long long)n * q / 32);
-      if (m < 1) continue;
-      int l = 0, t = 0;
-      for (int p = 0; p < m; ++p) l += dim[seq[p]];
-      for (int p = 0; p < m; ++p)
-        for (int u : adj[seq[p]]) mark[u] = 1;
-      for (int p = m; p < n; ++p)
-        if (mark[seq[p]]) t += dim[seq[p]];
-      for (int p = 0; p < m; ++p)
-        for (int u : adj[seq[p]]) mark[u] = 0;
-      const int chain = std::max(l, all - l - t) + t + kCholNB;
-      if (chain < best && all - l - t > 0) {
-        best = chain;
-        cut = m;
-      }
+  if (levels == 0 || n == 0) return;
+  // a keyframe is in T of the cuts between its first neighbour and itself:
+  // dims that join (and leave) T at each cut, from one pass over the neighbours
+  std::vector<int> first(n), join(n + 1, 0);
+  for (int p = 0; p < n; ++p) pos[seq[p]] = p;
+  int all = 0;
+  for (int p = 0; p < n; ++p) {
+    int f = p;
+    for (int u : adj[seq[p]])
+      if (pos[u] >= 0) f = std::min(f, pos[u]);
+    first[p] = f;
+    if (f < p) {
+      join[f + 1] += dim[seq[p]];
+      join[p + 1] -= dim[seq[p]];
+    }
+    all += dim[seq[p]];
+  }
+  for (int p = 0; p < n; ++p) pos[seq[p]] = -1;
+  // cuts at every 32nd of the sequence: the longest chain L or R, then T
+  int cut = -1, best = all, m = 0, l = 0, t = 0;
+  for (int q = 4; q <= 28; ++q) {
+    const int to = (int)((long long)n * q / 32);
+    if (to < 1) continue;
+    for (; m < to; ++m) {
+      l += dim[seq[m]];
+      t += join[m + 1];
+    }
+    const int chain = std::max(l, all - l - t) + t + kCholNB;
+    if (chain < best && all - l - t > 0) {
+      best = chain;
+      cut = m;
     }
   }
-  if (cut < 0) {
-    if (!out.empty()) out.push_back(-1);
-    out.insert(out.end(), seq.begin(), seq.end());
-    return;
-  }
-  std::vector<int> L(seq.begin(), seq.begin() + cut), R, T;
-  for (int a : L)
-    for (int u : adj[a]) mark[u] = 1;
-  for (int p = cut; p < n; ++p) (mark[seq[p]] ? T : R).push_back(seq[p]);
-  for (int a : L)
-    for (int u : adj[a]) mark[u] = 0;
-  std::reverse(R.begin(), R.end());
-  dissect(L, levels - 1, dim, adj, mark, out);
-  dissect(R, levels - 1, dim, adj, mark, out);
-  out.insert(out.end(), T.begin(), T.end());
+  if (cut < 0) return;
+  P.sides.resize(2);
+  P.sides[0].seq.assign(seq.begin(), seq.begin() + cut);
+  for (int p = n - 1; p >= cut; --p)
+    if (first[p] >= cut) P.sides[1].seq.push_back(seq[p]);
+  for (int p = cut; p < n; ++p)
+    if (first[p] < cut) P.T.push_back(seq[p]);
+  for (Parts& side : P.sides) dissect(side, levels - 1, dim, adj, pos);
 }
 
-// row at which each keyframe of a sequence starts (see dissect for -1); the
+// The order that the cuts of the first levels make, -1 where the next keyframe
+// has to start a tile of its own (with a tile shared between two parts the
+// second would wait for the first).
+void parts_order(const Parts& P, int levels, std::vector<int>& out) {
+  if (levels == 0 || P.sides.empty()) {
+    if (!out.empty()) out.push_back(-1);
+    out.insert(out.end(), P.seq.begin(), P.seq.end());
+    return;
+  }
+  for (const Parts& side : P.sides) parts_order(side, levels - 1, out);
+  out.insert(out.end(), P.T.begin(), P.T.end());
+}
+
+// row at which each keyframe of a sequence starts (see parts_order for -1); the
 // number of rows
 int sequence_rows(const std::vector<int>& seq, const std::vector<int>& dim, std::vector<int>& off) {
   off.assign(dim.size(), 0);
@@ -420,16 +441,19 @@ void tile_fill(const std::vector<int>& dim, const std::vector<Coupling>& cpl, co
   }
   // eliminating column j couples the rows below it in that column
   std::vector<int> rows;
+  std::vector<uint32_t> col(nw);
   E.depth.assign(nblk, 1);
   E.chain = 0;
   E.work = 0;
   for (int j = 0; j < nblk; ++j) {
     rows.clear();
+    std::fill(col.begin(), col.end(), 0u);
     for (int i = j + 1; i <= nblk; ++i)
-      if (E.has(nw, i, j)) rows.push_back(i);
-    for (size_t p = 0; p < rows.size(); ++p)
-      for (size_t q = 0; q <= p; ++q)
-        if (rows[q] < nblk) set(rows[p], rows[q]);
+      if (E.has(nw, i, j)) {
+        rows.push_back(i);
+        if (i < nblk) col[i >> 5] |= 1u << (i & 31);
+        for (int w = j >> 5; w <= std::min(i >> 5, nw - 1); ++w) E.nz[(size_t)i * nw + w] |= col[w];
+      }
     for (int i : rows)
       if (i < nblk) E.depth[i] = std::max(E.depth[i], E.depth[j] + 1);
     E.chain = std::max(E.chain, E.depth[j]);
@@ -576,25 +600,41 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
       for (int a = 0; a < W.N; ++a)
         if (sep[a]) dim[a] = 15;
     }
-    std::vector<std::vector<std::pair<int, int>>> items((size_t)W.N * W.N);
-    for (int g = W.kf_base; g < W.kf_base + W.N; ++g) {
-      const int k = cnt[g];
-      std::vector<int> T(1, g - W.kf_base);
-      for (int s = P.src_off[g]; s < P.src_off[g + 1]; ++s) T.push_back(P.jj[P.src_edges[s]] - W.kf_base);
-      for (int ta = 0; ta <= k; ++ta)
-        for (int tb = 0; tb <= k; ++tb)
-          items[(size_t)T[ta] * W.N + T[tb]].push_back({P.z_off[g] + (ta * (k + 1) + tb) * ZD, P.zb_off[g] + ZBD * ta});
-    }
-    if (pg) {
-      for (int f = 0; f < P.R; ++f) {
-        const int i = P.rel_ii[f], j = P.rel_jj[f];
-        const int zf = P.rel_z[f], zbf = P.rel_zb[f];
-        items[(size_t)i * W.N + i].push_back({zf, zbf});
-        items[(size_t)i * W.N + j].push_back({zf + 49, zbf});
-        items[(size_t)j * W.N + i].push_back({zf + 98, zbf + 7});
-        items[(size_t)j * W.N + j].push_back({zf + 147, zbf + 7});
+    // the window's pair table: for (a, b) the Z blocks that add to it, sources
+    // in order, then relative poses (counted, then filled in the same order);
+    // entries pair_base .. pair_base + N*N, the last one its end
+    auto each_block = [&](auto&& put) {
+      for (int g = W.kf_base; g < W.kf_base + W.N; ++g) {
+        const int k = cnt[g];
+        int T[kMaxOutDegree + 1] = {g - W.kf_base};
+        for (int s = 0; s < k; ++s) T[s + 1] = P.jj[P.src_edges[P.src_off[g] + s]] - W.kf_base;
+        for (int ta = 0; ta <= k; ++ta)
+          for (int tb = 0; tb <= k; ++tb) put(T[ta], T[tb], P.z_off[g] + (ta * (k + 1) + tb) * ZD, P.zb_off[g] + ZBD * ta);
       }
-    }
+      for (int f = 0; f < (pg ? P.R : 0); ++f) {
+        const int i = P.rel_ii[f], j = P.rel_jj[f], zf = P.rel_z[f], zbf = P.rel_zb[f];
+        put(i, i, zf, zbf);
+        put(i, j, zf + 49, zbf);
+        put(j, i, zf + 98, zbf + 7);
+        put(j, j, zf + 147, zbf + 7);
+      }
+    };
+    W.pair_base = (int)P.pair_off.size();
+    const size_t NN = (size_t)W.N * W.N, pair_at = P.pair_z.size();
+    P.pair_off.resize(W.pair_base + NN + 1, 0);
+    int32_t* poff = P.pair_off.data() + W.pair_base;
+    each_block([&](int a, int b, int, int) { ++poff[(size_t)a * W.N + b + 1]; });
+    poff[0] = (int32_t)pair_at;
+    for (size_t q = 0; q < NN; ++q) poff[q + 1] += poff[q];
+    P.pair_z.resize(poff[NN]);
+    P.pair_zb.resize(poff[NN]);
+    std::vector<int32_t> next_pair(poff, poff + NN);
+    each_block([&](int a, int b, int z, int zb) {
+      const int32_t at = next_pair[(size_t)a * W.N + b]++;
+      P.pair_z[at] = z;
+      P.pair_zb[at] = zb;
+    });
+    auto coupled = [&](int a, int b) { return poff[(size_t)a * W.N + b + 1] > poff[(size_t)a * W.N + b]; };
     // couplings of S: the vision terms couple only the 6 pose unknowns at the
     // head of each keyframe's block (all 7 in the pose graph); a segment couples
     // all of its columns (poses of the segment and its neighbours, V of the
@@ -603,7 +643,7 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
     std::vector<std::vector<int>> adj(W.N);
     for (int a = 0; a < W.N; ++a)
       for (int b = 0; b < a; ++b)
-        if (!items[(size_t)a * W.N + b].empty()) cpl.push_back({a, b, pg, pg});
+        if (coupled(a, b)) cpl.push_back({a, b, pg, pg});
     for (const SegDev& S : cond.segs)
       for (int a = S.k0; a <= S.k1; ++a)
         for (int b = S.k0; b < a; ++b) cpl.push_back({a, b, true, true});
@@ -663,14 +703,20 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
           for (auto& v : adj2) v.erase(std::remove(v.begin(), v.end(), hub), v.end());
           adj2[hub].clear();
         }
-        std::vector<char> mark(W.N, 0);
-        for (std::vector<int> base : {seq, hub >= 0 ? rcm_order(W.N, adj2) : rcm}) {
-          base.erase(std::remove(base.begin(), base.end(), hub), base.end());
+        std::vector<int> pos(W.N, -1);
+        for (const std::vector<int>& base : {seq, hub >= 0 ? rcm_order(W.N, adj2) : rcm}) {
+          Parts parts;
+          for (int a : base)
+            if (a != hub) parts.seq.push_back(a);
+          dissect(parts, kCutLevels, dim, adj2, pos);
+          std::vector<int> q, before;
           for (int levels = 1; levels <= kCutLevels; ++levels) {
-            std::vector<int> q;
-            dissect(base, levels, dim, adj2, mark, q);
+            q.clear();
+            parts_order(parts, levels, q);
             if (hub >= 0) q.push_back(hub);
+            if (q == before) break;                 // no further cut
             consider(q);
+            before = q;
           }
         }
       }
@@ -755,16 +801,6 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
       }
       for (uint32_t v : env.nz) P.chol_tab.push_back((int32_t)v);
     }
-    // this window's table: entries pair_base .. pair_base + N*N (the last one is its end)
-    W.pair_base = (int)P.pair_off.size();
-    for (size_t q = 0; q < items.size(); ++q) {
-      P.pair_off.push_back((int32_t)P.pair_z.size());
-      for (auto& it : items[q]) {
-        P.pair_z.push_back(it.first);
-        P.pair_zb.push_back(it.second);
-      }
-    }
-    P.pair_off.push_back((int32_t)P.pair_z.size());
   }
   if (P.pair_z.empty()) { P.pair_z.push_back(0); P.pair_zb.push_back(0); }
   // Cholesky tickets of the windows too large for the one-workgroup path, by
