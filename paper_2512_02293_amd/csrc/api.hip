@@ -34,6 +34,19 @@ struct WinIn {
   const vi_rel_poses* rel = nullptr;      // pose-graph adjustment: relative-pose factors (marks the mode)
 };
 
+// A plan and its tables on the device.
+struct PlanSlot {
+  Plan plan;
+  bool have_plan = false;
+  uint64_t version = 0;
+  std::vector<int32_t> sig;        // shape signature of the planned batch
+  char* d_plan = nullptr;
+  size_t d_plan_cap = 0;
+  DevPlan dplan{};
+  WinDev* d_win = nullptr;         // device window table (inside d_plan)
+  std::vector<char> win_on_dev;    // bytes d_win holds (empty: not known), so an unchanged table is not sent again
+};
+
 }  // namespace
 
 struct vi_ctx {
@@ -47,16 +60,12 @@ struct vi_ctx {
   int32_t* d_off = nullptr;        // device CSR for imu_preintegrate
   size_t d_off_cap = 0;
   std::vector<int32_t> off_on_dev; // what d_off holds (empty: not known), so an unchanged CSR is not sent again
-  // plan
-  Plan plan;
-  bool have_plan = false;
+  // plans: of the last batch with inertial factors and of the last one without
+  // (their reduced systems differ), so that a program that alternates between
+  // both on one frame graph keeps either
+  PlanSlot slots[2];
+  PlanSlot* at = &slots[0];        // of the current call
   uint64_t plan_version = 0;
-  std::vector<int32_t> plan_sig;   // shape signature of the planned batch
-  char* d_plan = nullptr;
-  size_t d_plan_cap = 0;
-  DevPlan dplan{};
-  WinDev* d_win = nullptr;         // device window table (inside d_plan)
-  std::vector<char> win_on_dev;    // bytes d_win holds (empty: not known), so an unchanged table is not sent again
   int attr_kmax = -1, attr_cond = -1;
   // autotuning
   bool autotune = false;
@@ -141,11 +150,12 @@ vi_status check_opts(vi_ctx* ctx, const vi_opts* o) {
   return VI_OK;
 }
 
-// Shape signature: everything the plan depends on (sizes and the frame graphs).
-std::vector<int32_t> plan_signature(const std::vector<WinIn>& wins, bool use_imu, bool bias_global) {
+// Shape signature: everything the plan depends on (sizes and the frame graphs)
+// beside whether there are inertial factors, which selects the slot.
+std::vector<int32_t> plan_signature(const std::vector<WinIn>& wins, bool bias_global) {
   std::vector<int32_t> s;
+  s.push_back(bias_global ? 1 : 0);
   s.push_back((int32_t)wins.size());
-  s.push_back((use_imu ? 2 : 0) | (bias_global ? 1 : 0));
   for (const WinIn& in : wins) {
     s.push_back(in.st->n_kf);
     s.push_back(in.cam->H);
@@ -963,10 +973,10 @@ Work do_carve(const Plan& P, void* base, size_t* bytes) {
 
 // Upload the int tables; the window table at the front is refreshed per call.
 vi_status upload_plan(vi_ctx* ctx) {
-  const Plan& P = ctx->plan;
+  const Plan& P = ctx->at->plan;
   std::vector<int32_t> segs(P.segs.size() * (sizeof(SegDev) / 4));
   if (!segs.empty()) std::memcpy(segs.data(), P.segs.data(), segs.size() * 4);
-  DevPlan& D = ctx->dplan;
+  DevPlan& D = ctx->at->dplan;
   const int32_t* dsegs = nullptr;
   // each table and the device pointer that receives its place
   struct Part { const std::vector<int32_t>* v; const int32_t** dst; };
@@ -979,24 +989,24 @@ vi_status upload_plan(vi_ctx* ctx) {
                         {&P.kf_seg, &D.kf_seg}, {&P.f_seg, &D.f_seg}, {&P.gram_map, &D.gram_map}, {&segs, &dsegs}};
   size_t total = align256(sizeof(WinDev) * P.n_win);
   for (const Part& p : parts) total += align256(std::max<size_t>(p.v->size(), 1) * sizeof(int32_t));
-  if (total > ctx->d_plan_cap) {
-    if (ctx->d_plan) HIPCHK(ctx, hipFree(ctx->d_plan));
-    ctx->d_plan = nullptr;
-    HIPCHK(ctx, hipMalloc((void**)&ctx->d_plan, total));
-    ctx->d_plan_cap = total;
+  if (total > ctx->at->d_plan_cap) {
+    if (ctx->at->d_plan) HIPCHK(ctx, hipFree(ctx->at->d_plan));
+    ctx->at->d_plan = nullptr;
+    HIPCHK(ctx, hipMalloc((void**)&ctx->at->d_plan, total));
+    ctx->at->d_plan_cap = total;
   }
   std::vector<char> host(total, 0);
   size_t off = align256(sizeof(WinDev) * P.n_win);
   for (const Part& p : parts) {
     if (!p.v->empty()) std::memcpy(host.data() + off, p.v->data(), p.v->size() * sizeof(int32_t));
-    *p.dst = (const int32_t*)(ctx->d_plan + off);
+    *p.dst = (const int32_t*)(ctx->at->d_plan + off);
     off += align256(std::max<size_t>(p.v->size(), 1) * sizeof(int32_t));
   }
   D.segs = (const SegDev*)dsegs;
-  ctx->win_on_dev.clear();
-  HIPCHK(ctx, hipMemcpy(ctx->d_plan, host.data(), total, hipMemcpyHostToDevice));
-  ctx->d_win = (WinDev*)ctx->d_plan;
-  D.win = ctx->d_win;
+  ctx->at->win_on_dev.clear();
+  HIPCHK(ctx, hipMemcpy(ctx->at->d_plan, host.data(), total, hipMemcpyHostToDevice));
+  ctx->at->d_win = (WinDev*)ctx->at->d_plan;
+  D.win = ctx->at->d_win;
   return VI_OK;
 }
 
@@ -1010,24 +1020,33 @@ vi_status ensure_status(vi_ctx* ctx, int n) {
 }
 
 vi_status ensure_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, bool use_imu, bool bias_global) {
-  std::vector<int32_t> sig = plan_signature(wins, use_imu, bias_global);
-  if (ctx->have_plan && sig == ctx->plan_sig) return VI_OK;
+  std::vector<int32_t> sig = plan_signature(wins, bias_global);
+  PlanSlot& S = ctx->slots[use_imu ? 1 : 0];
+  const PlanSlot& other = *ctx->at;
+  // another plan of the same graph hands over its tiling of the assembly
+  const bool twin = &other != &S && other.have_plan && other.sig.size() == sig.size() &&
+                    std::equal(sig.begin() + 1, sig.end(), other.sig.begin() + 1);
+  ctx->at = &S;
+  if (S.have_plan && sig == S.sig) {
+    if (twin) set_range(S.plan, other.plan.range);
+    return VI_OK;
+  }
   Plan P;
   vi_status s = build_plan(ctx, wins, P, use_imu, bias_global);
   if (s != VI_OK) return s;
-  set_range(P, default_range(P));
-  ctx->plan = std::move(P);
-  ctx->plan_sig = std::move(sig);
-  ctx->have_plan = false;
+  set_range(P, twin ? other.plan.range : default_range(P));
+  S.plan = std::move(P);
+  S.sig = std::move(sig);
+  S.have_plan = false;
   s = upload_plan(ctx);
   if (s != VI_OK) return s;
-  s = ensure_status(ctx, ctx->plan.n_win);
+  s = ensure_status(ctx, S.plan.n_win);
   if (s != VI_OK) return s;
-  ctx->have_plan = true;
-  ctx->plan_version++;
-  if (ctx->plan.kmax > ctx->attr_kmax || ctx->plan.cond_len > ctx->attr_cond) {
-    ctx->attr_kmax = std::max(ctx->attr_kmax, ctx->plan.kmax);
-    ctx->attr_cond = std::max(ctx->attr_cond, ctx->plan.cond_len);
+  S.have_plan = true;
+  S.version = ++ctx->plan_version;
+  if (S.plan.kmax > ctx->attr_kmax || S.plan.cond_len > ctx->attr_cond) {
+    ctx->attr_kmax = std::max(ctx->attr_kmax, S.plan.kmax);
+    ctx->attr_cond = std::max(ctx->attr_cond, S.plan.cond_len);
     step_set_attributes(ctx->attr_kmax, ctx->attr_cond);
     pg_set_attributes();
   }
@@ -1054,7 +1073,7 @@ void extrinsic_rotation(const double* T, double* R, double* t, int* ext) {
 
 // this call's window pointers -> host window table -> device
 vi_status refresh_windows(vi_ctx* ctx, const std::vector<WinIn>& wins, bool depth_f32 = false) {
-  Plan& P = ctx->plan;
+  Plan& P = ctx->at->plan;
   for (int w = 0; w < P.n_win; ++w) {
     WinDev& W = P.win[w];
     const WinIn& in = wins[w];
@@ -1075,10 +1094,10 @@ vi_status refresh_windows(vi_ctx* ctx, const std::vector<WinIn>& wins, bool dept
   // a blocking copy: send it only when the table differs from what the device holds
   const size_t nb = sizeof(WinDev) * P.n_win;
   const char* hb = (const char*)P.win.data();
-  if (ctx->win_on_dev.size() == nb && std::memcmp(ctx->win_on_dev.data(), hb, nb) == 0) return VI_OK;
-  ctx->win_on_dev.clear();
-  HIPCHK(ctx, hipMemcpy(ctx->d_win, hb, nb, hipMemcpyHostToDevice));
-  ctx->win_on_dev.assign(hb, hb + nb);
+  if (ctx->at->win_on_dev.size() == nb && std::memcmp(ctx->at->win_on_dev.data(), hb, nb) == 0) return VI_OK;
+  ctx->at->win_on_dev.clear();
+  HIPCHK(ctx, hipMemcpy(ctx->at->d_win, hb, nb, hipMemcpyHostToDevice));
+  ctx->at->win_on_dev.assign(hb, hb + nb);
   return VI_OK;
 }
 
@@ -1096,7 +1115,7 @@ void mark_event(void* user, int stage_done) {
 // keep the fastest for this batch shape.  The candidates run the assembly and
 // local-block stages only, which write the workspace, never the caller's state.
 vi_status autotune_range(vi_ctx* ctx, const Work& w, const OptsDev& od) {
-  Plan& P = ctx->plan;
+  Plan& P = ctx->at->plan;
   const bool pg = P.pdim == 7;
   const auto key = std::make_tuple(P.hw_max, P.kmax, P.N, P.n_win * (pg ? -1 : 1));
   auto it = ctx->tuned.find(key);
@@ -1108,7 +1127,7 @@ vi_status autotune_range(vi_ctx* ctx, const Work& w, const OptsDev& od) {
   hipEvent_t ev[kNumStages + 1];
   for (auto& e : ev) HIPCHK(ctx, hipEventCreate(&e));
   launch_reset_status(sp, ctx->status, P.n_win, w.seg_cnt, (int)P.segs.size());
-  if (od.use_imu) launch_imu_info(sp, P, ctx->dplan, w.Lam, ctx->status);
+  if (od.use_imu) launch_imu_info(sp, P, ctx->at->dplan, w.Lam, ctx->status);
   TimingUser tu{sp, ev};
   int best = default_range(P);
   float best_ms = 1e30f;
@@ -1120,18 +1139,18 @@ vi_status autotune_range(vi_ctx* ctx, const Work& w, const OptsDev& od) {
     if (whole) break;
     whole = r >= P.hw_max;
     set_range(P, r);
-    ctx->win_on_dev.clear();
-    HIPCHK(ctx, hipMemcpy(ctx->d_win, P.win.data(), sizeof(WinDev) * P.n_win, hipMemcpyHostToDevice));
+    ctx->at->win_on_dev.clear();
+    HIPCHK(ctx, hipMemcpy(ctx->at->d_win, P.win.data(), sizeof(WinDev) * P.n_win, hipMemcpyHostToDevice));
     float tot = 0.f;
     for (int rep = 0; rep < 3; ++rep) {
       HIPCHK(ctx, hipEventRecord(ev[0], sp));
       if (pg) {
         // pose graph: the fused assembly of the loop pairs and the per-source blocks
-        launch_vis_assembly(sp, P, ctx->dplan, w, od, ctx->status);
-        launch_pg_local(sp, P, ctx->dplan, w, od, ctx->status);
+        launch_vis_assembly(sp, P, ctx->at->dplan, w, od, ctx->status);
+        launch_pg_local(sp, P, ctx->at->dplan, w, od, ctx->status);
         HIPCHK(ctx, hipEventRecord(ev[kStLocal + 1], sp));
       } else {
-        launch_tune_stages(sp, P, ctx->dplan, w, od, mark_event, &tu);
+        launch_tune_stages(sp, P, ctx->at->dplan, w, od, mark_event, &tu);
       }
       HIPCHK(ctx, hipEventSynchronize(ev[kStLocal + 1]));
       float ms = 0.f;
@@ -1235,7 +1254,7 @@ vi_status run(vi_ctx* ctx, const std::vector<WinIn>& wins, const vi_opts* o, int
   HIPCHK(ctx, hipSetDevice(ctx->device));
   s = ensure_plan(ctx, wins, o->use_imu != 0, o->use_imu && o->bias_mode == VI_BIAS_GLOBAL);
   if (s != VI_OK) return s;
-  Plan& P = ctx->plan;
+  Plan& P = ctx->at->plan;
   size_t need = 0;
   if (wa)
     warm_carve(P, wa->hq, wa->wq, nullptr, &need);
@@ -1262,7 +1281,7 @@ vi_status run(vi_ctx* ctx, const std::vector<WinIn>& wins, const vi_opts* o, int
     s = refresh_windows(ctx, wins, o->invdepth_f32 != 0);
     if (s != VI_OK) return s;
   }
-  const DevPlan& D = ctx->dplan;
+  const DevPlan& D = ctx->at->dplan;
 
   if (timing) {
     std::vector<hipEvent_t> ev(kNumStages + 1);
@@ -1293,7 +1312,7 @@ vi_status run(vi_ctx* ctx, const std::vector<WinIn>& wins, const vi_opts* o, int
     for (auto& e : ev) (void)hipEventDestroy(e);
   } else {
     std::vector<uint64_t> key;
-    key.push_back(ctx->plan_version);
+    key.push_back(ctx->at->version);
     key.push_back((uint64_t)iters);
     key.push_back((uint64_t)P.range);
     uint64_t tb;
@@ -1436,7 +1455,7 @@ vi_status run_pgba(vi_ctx* ctx, const vi_camera* cam, int32_t n_kf, double* pose
   std::vector<WinIn> wins{in};
   s = ensure_plan(ctx, wins, false, false);
   if (s != VI_OK) return s;
-  Plan& P = ctx->plan;
+  Plan& P = ctx->at->plan;
   size_t need = 0;
   do_carve(P, nullptr, &need);
   if (workspace_bytes < need)
@@ -1454,7 +1473,7 @@ vi_status run_pgba(vi_ctx* ctx, const vi_camera* cam, int32_t n_kf, double* pose
     s = refresh_windows(ctx, wins);
     if (s != VI_OK) return s;
   }
-  const DevPlan& D = ctx->dplan;
+  const DevPlan& D = ctx->at->dplan;
   const int ncost = cost_slots(P);
   launch_reset_status(sp, ctx->status, P.n_win);
   for (int it = 0; it < iters; ++it) {
@@ -1535,7 +1554,8 @@ void vi_ctx_destroy(vi_ctx* c) {
   if (c->priv) (void)hipStreamSynchronize(c->priv);
   if (c->exec) (void)hipGraphExecDestroy(c->exec);
   if (c->graph) (void)hipGraphDestroy(c->graph);
-  if (c->d_plan) (void)hipFree(c->d_plan);
+  for (PlanSlot& S : c->slots)
+    if (S.d_plan) (void)hipFree(S.d_plan);
   if (c->d_off) (void)hipFree(c->d_off);
   if (c->status) (void)hipFree(c->status);
   if (c->ev_in) (void)hipEventDestroy(c->ev_in);
@@ -1794,7 +1814,7 @@ vi_status vi_warm_features(vi_ctx* ctx, int32_t n_windows, const vi_window* wind
   OptsDev od{opts->n_fixed, opts->use_imu ? 1 : 0, opts->bias_mode == VI_BIAS_FIXED ? 1 : 0, opts->precision, opts->lm_lambda,
              opts->depth_eta, opts->z_min, opts->d_min, 0.0,
              (opts->use_imu && opts->bias_mode == VI_BIAS_GLOBAL) ? 1 : 0};
-  launch_warm_features(ctx->priv, ctx->plan, ctx->dplan, od, hq, wq, feat, dims);
+  launch_warm_features(ctx->priv, ctx->at->plan, ctx->at->dplan, od, hq, wq, feat, dims);
   return warm_end(ctx);
 }
 
@@ -1869,7 +1889,7 @@ vi_status vi_warm_apply(vi_ctx* ctx, int32_t n_windows, const vi_window* windows
   s = warm_windows(ctx, n_windows, windows, opts, hq, wq, wins);
   if (s != VI_OK) return s;
   if ((s = warm_begin(ctx)) != VI_OK) return s;
-  launch_warm_apply(ctx->priv, ctx->plan, ctx->dplan, hq, wq, dd, db, opts->d_min,
+  launch_warm_apply(ctx->priv, ctx->at->plan, ctx->at->dplan, hq, wq, dd, db, opts->d_min,
                     (opts->use_imu && opts->bias_mode == VI_BIAS_PER_KF) ? 1 : 0);
   return warm_end(ctx);
 }
