@@ -358,13 +358,15 @@ void scalar_envelope(const std::vector<int>& dim, const std::vector<Coupling>& c
 }
 
 // Separator keyframes of a window of N keyframes (see kCondSpan): about every
-// kCondSpan, more where the padding of the last tile takes their unknowns
+// kCondSpan, more where the padding of the last tile takes their unknowns, all
+// of them where the elimination does not pay (see cond_pays)
 std::vector<char> cond_separators(int N, bool bias_global) {
-  std::vector<char> sep(N, 0);
   int nseg = (N + kCondSpan) / (kCondSpan + 1);
   const int n0 = 6 * N + (bias_global ? kCondNV : 0);
   auto tiles = [&](int segs) { return (n0 + kCondNV * (segs - 1) + kCholNB - 1) / kCholNB; };
   while (tiles(nseg + 1) == tiles(nseg) && (N - nseg) / (nseg + 1) >= kCondMinLen) ++nseg;
+  if (!cond_pays(N, bias_global, (15 * N + kCholNB - 1) / kCholNB - tiles(nseg))) return std::vector<char>(N, 1);
+  std::vector<char> sep(N, 0);
   for (int j = 1; j < nseg; ++j) sep[(size_t)((long long)j * N / nseg)] = 1;
   if (bias_global) sep[N - 1] = 1;
   return sep;
@@ -657,6 +659,9 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
     for (const SegDev& S : cond.segs)
       for (int a = S.k0; a <= S.k1; ++a)
         for (int b = S.k0; b < a; ++b) cpl.push_back({a, b, true, true});
+    // the factor between two separators is in no segment
+    for (int a = 0; a + 1 < W.N; ++a)
+      if (dim[a] == 15 && dim[a + 1] == 15) cpl.push_back({a + 1, a, true, true});
     // one bias for the window: it sits in the last keyframe's slot and couples
     // with every keyframe that an inertial factor touches
     if (!pg && use_imu && bias_global)

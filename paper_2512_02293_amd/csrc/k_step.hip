@@ -637,11 +637,13 @@ __device__ __forceinline__ bool vis_other_work(const OptsDev& o, const DevPlan& 
       // its velocity and bias unknowns: nobody waits, and the counter is back
       // at zero for the next launch
       __shared__ int last;
-      const SegDev& S = D.segs[D.f_seg[f]];
+      const int seg = D.f_seg[f];
+      if (seg < 0) return true;              // between two separators
+      const SegDev& S = D.segs[seg];
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's blocks have arrived
       __syncthreads();
       if (tid == 0) {
-        int* cnt = seg_cnt + D.f_seg[f];
+        int* cnt = seg_cnt + seg;
         const int before = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         last = before == S.nf - 1;
         if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

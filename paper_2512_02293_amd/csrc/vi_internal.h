@@ -46,9 +46,21 @@ constexpr int kTraceLen = 2 * (kMaxIters + 1);
 //    costs nothing there and halves a chain, so more are taken while segments
 //    keep kCondMinLen keyframes (12 keyframes: 513 -> 465 us; at 6, segments of
 //    3 and 2 keyframes, 443 -> 449).
+//  * The elimination takes 6 to 12 us an iteration in windows of up to 7
+//    keyframes, with one bias for the window 14 to 18, and saves the
+//    factorisation 8 to 10 for each tile column that the reduced system is
+//    shorter by.  Where it saves too few, every keyframe keeps its V (a
+//    separator): us of a call of 8 iterations, all kept / eliminated, 40 x 56
+//    maps: 2 keyframes (no column saved) 495 / 558, 3 (one) 578 / 566, 4 (one)
+//    583 / 591, 6 (one) 665 / 701, 5 (two) 663 / 594, 7 (two) 741 / 682; with one
+//    bias 3 (one) 581 / 621, 4 (none) 590 / 715, 6 (one) 675 / 741, 7 (two) 749 /
+//    734, 8 (two) 753 / 752.
 constexpr int kCondSpan = 12;
 constexpr int kCondMinLen = 3;
 constexpr int kCondNV = 9;
+constexpr bool cond_pays(int N, bool bias_global, int tiles_saved) {
+  return tiles_saved > 1 || (tiles_saved == 1 && !bias_global && N <= 3);
+}
 // Device status word of one window: first error (vi_status), its detail (e.g.
 // pivot index), the number of committed steps, whether the tolerance stopped it,
 // and what the elimination of velocities and biases found (elim).  That runs
@@ -143,7 +155,7 @@ struct Plan {
   std::vector<int32_t> kf_off, row_map;
   std::vector<SegDev> segs;
   std::vector<int32_t> kf_seg;                 // [2 N] segments whose columns hold the keyframe's pose (-1: none)
-  std::vector<int32_t> f_seg;                  // [F] segment that eliminates with the factor
+  std::vector<int32_t> f_seg;                  // [F] segment that eliminates with the factor, -1: between two separators
   std::vector<int32_t> gram_map;               // (segment, first Gram tile) per workgroup of the segments' Grams
   int cond_len = 0;                            // keyframes of the longest segment
   // per window of the dataflow path: chain order of the block columns, the ends
