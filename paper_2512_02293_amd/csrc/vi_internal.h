@@ -68,9 +68,10 @@ constexpr bool cond_pays(int N, bool bias_global, int tiles_saved) {
 // the order of errors (a non-finite entry with the assembly's, a pivot with the
 // factorisation's), so it is kept apart: kElimNonfinite or kElimPivot, plus
 // kElimPivot - 1 minus the coordinate (keyframe * 15 + unknown), the largest
-// kept; 0: nothing.
+// kept; 0: nothing.  32 bytes, so that it is found by a shift: with 20 every
+// launch paid for it (inertial initialisation 1037 -> 1050 us).
 constexpr int kElimPivot = 1 << 20, kElimNonfinite = 1 << 21;
-struct DevStatus {
+struct alignas(32) DevStatus {
   int code;
   int detail;
   int iters;
