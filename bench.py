@@ -5,9 +5,10 @@ each keyframe to its 12 nearest by index, 200 Hz IMU with 20 samples per
 keyframe gap), seeded synthetic data.  One benchmark step is one whole pass of
 the hot path: IMU preintegration of the window's 23 factors, then a solve of 8
 damped Gauss-Newton iterations (each: residual/Jacobian assembly, inertial
-factors, Schur elimination of the inverse depths, FP64 Cholesky of the 360x360
-reduced system, back-substitution and retraction) and the final cost, all in
-FP64, replayed from one captured HIP graph.  Every step restarts from the same
+factors, elimination of the inverse depths and of the velocities and biases,
+FP64 Cholesky of the reduced system of the 24 poses, back-substitution and
+retraction) and the final cost, all in FP64, replayed from one captured HIP
+graph.  Every step restarts from the same
 initial estimate (a device-to-device copy of the four state arrays, inside the
 timed region).
 
@@ -99,20 +100,22 @@ def stage_models(prob):
       (6k+1)(6k+2) flops.  Residual/Jacobian evaluation is not counted.
       Its HBM side is 16 B per pixel-residual (f32 target and weight) plus
       8 B in and 16 B out per source pixel.
-    cholesky (FP64): n^3/3 flops for the 15N x 15N reduced system.
+    cholesky (FP64): n^3/3 flops for the n = 6 N pose unknowns, which no
+      elimination ahead of it takes away (the library's system holds a few
+      velocities and biases beside them).
     """
     import numpy as np
     N, E, HW = prob.n_kf, prob.n_edges, prob.H * prob.W
     ks = np.bincount(prob.ii, minlength=N)
     gram_flops = float(sum((6 * k + 1) * (6 * k + 2) for k in ks if k > 0)) * HW
-    n = 15 * N
+    n = 6 * N
     return {
         "vis_gram_imu": dict(bound="mfma", unit="TFLOP/s", peak=FP64_PEAK_TFLOPS, scale=1e12,
                              work=gram_flops + 132.0 * E * HW, work_name="algorithmic_flops_per_launch",
                              per_unit="132 flops per pixel-residual + (6k+1)(6k+2) flops per source pixel",
                              hbm_bytes=float(E * HW * 16 + N * HW * 24)),
         "cholesky": dict(bound="mfma", unit="TFLOP/s", peak=FP64_PEAK_TFLOPS, scale=1e12, work=n ** 3 / 3.0,
-                         work_name="algorithmic_flops_per_launch", per_unit="n^3/3 flops, n = 15 N",
+                         work_name="algorithmic_flops_per_launch", per_unit="n^3/3 flops, n = 6 N",
                          note="one window is one 512-thread workgroup on one CU (FP64 MFMA peak of one CU: "
                               "78.6/256 = 0.307 TFLOP/s); the factor's critical path is a chain of 32x32 "
                               "diagonal-tile factorisations"),
@@ -423,8 +426,8 @@ def global_problem(ctx, iters=2, reps=3):
     prob = synth.make_problem(synth.config_global(), 3)
     dp = binding.DeviceProblem(prob)
     imu = ctx.imu_preintegrate(dp.off, dp.gyro, dp.accel, dp.imu_dt, dp.bias_hat, dp.noise)
-    res = {"workload": "512 keyframes, 60x80 maps, 5832 edges (11 nearest + 200 loop edges), reduced system "
-                       "7680 x 7680; GN iterations from the initial state"}
+    res = {"workload": "512 keyframes, 60x80 maps, 5832 edges (11 nearest + 200 loop edges), 7680 keyframe "
+                       "unknowns; GN iterations from the initial state"}
     for name, prec in (("fp64", binding.VI_PREC_FP64), ("mixed", binding.VI_PREC_MIXED)):
         o = binding.make_opts(precision=prec)
         ws = torch.empty(ctx.workspace_size(dp.cam, prob.n_kf, dp.ii, dp.jj, o), dtype=torch.uint8, device="cuda:0")
@@ -462,8 +465,8 @@ def pgba_loop_closure(ctx, iters=4, reps=3, cpu=True):
     pg = binding.DevicePGBA(prob)
     pxres = prob.n_edges * prob.H * prob.W
     res = {"workload": f"loop closure, {prob.n_kf} keyframes (Sim(3), 7 unknowns each), {prob.n_edges} loop pairs "
-                       f"of 60x80 maps, {len(prob.rel_ii)} relative poses (next 3 keyframes), reduced system "
-                       f"{7 * prob.n_kf} x {7 * prob.n_kf}; {iters} GN steps from the initial state",
+                       f"of 60x80 maps, {len(prob.rel_ii)} relative poses (next 3 keyframes), "
+                       f"{7 * prob.n_kf} keyframe unknowns; {iters} GN steps from the initial state",
            "pixel_residuals_per_gn_iter": pxres, "relative_poses": int(len(prob.rel_ii))}
     for name, prec in (("fp64", binding.VI_PREC_FP64), ("mixed", binding.VI_PREC_MIXED)):
         o = binding.make_opts(use_imu=False, precision=prec)
@@ -671,8 +674,8 @@ def inertial_init(ctx, n=64, n_kf=20, iters=10, reps=5):
             "workload": f"{n} problems of {n_kf} keyframes (200 Hz IMU, 0.1 s gaps), visual poses with 0.2 mm / "
                         f"0.01 deg errors, frame tilted 25 deg and shrunk by e^-0.9, {iters} iterations, FP64",
             "ms_per_call": 1e3 * best, "median_cost_reduction": float(np.median(c[:, -1] / c[:, 0])),
-            "roofline": {"bound": "latency", "note": "one 256-thread workgroup per problem; about 3 barriers per "
-                                                     "keyframe per iteration in the block Cholesky"}}
+            "roofline": {"bound": "latency", "note": "one 256-thread workgroup per problem; a chain of one 9x9 "
+                                                     "factor per keyframe and iteration, on one wave"}}
 
 
 def warm_windows(ctx, n=8, iters=5, reps=6):

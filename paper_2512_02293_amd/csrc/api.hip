@@ -473,9 +473,9 @@ void tile_fill(const std::vector<int>& dim, const std::vector<Coupling>& cpl, co
   }
 }
 
-// Relative time of the dataflow factorisation: its block columns take about 10 us each one after the other, beside which the tile
-// updates of a column (about 1 us on one of some 250 waves at a time) hardly
-// count.
+// Relative time of the dataflow factorisation: the block columns of a chain take
+// about 10 us each, one after the other, beside which the tile updates of a
+// column (about 1 us on one of some 250 waves at a time) hardly count.
 double dataflow_cost(const Order& E) { return E.chain + (double)E.work / 2500.0; }
 
 vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool use_imu, bool bias_global) {
@@ -854,7 +854,8 @@ vi_status build_plan(vi_ctx* ctx, const std::vector<WinIn>& wins, Plan& P, bool 
     }
   P.n_tickets = (int)(P.chol_tiles.size() / 2);
   // then the back-substitution's block columns, last column first, two per
-  // ticket where both are of one chain (c and c - 1: kPairTicketFlag)
+  // ticket where the second waits for the first (tile (c, c - 1) is nonzero:
+  // kPairTicketFlag)
   std::vector<int> next(nw);
   for (int w = 0; w < nw; ++w) next[w] = P.win[w].npad <= kCholSmallMaxNpad ? -1 : P.win[w].nblk - 1;
   for (bool more = true; more;) {

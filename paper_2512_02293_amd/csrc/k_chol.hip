@@ -1,4 +1,5 @@
-// FP64 Cholesky solve of the reduced pose/velocity/bias system of Eq. 4.
+// FP64 Cholesky solve of the reduced system of Eq. 4 (poses, and the velocities
+// and biases that are not eliminated before).
 //
 // The matrix buffer of a window holds S (npad x npad, row-major, lower
 // triangle used) followed by a 32-row right-hand-side block whose first row is
@@ -18,9 +19,9 @@
 // and publishes the result with a flag; k runs over the columns in which both
 // tiles are nonzero in the factor, zero tiles are not formed at all.  Tiles are
 // handed out by an atomic ticket counter in chain order (the position of column
-// j in its chain, then window, column and row i), and a tile only ever waits for tiles of smaller tickets, which were
-// taken by running workgroups: every wait ends without any assumption on
-// how many workgroups are resident.  Every wait is also bounded: past the
+// j in its chain, then window, column and row i), and a tile only ever waits for
+// tiles of smaller tickets, which were taken by running workgroups: every wait
+// ends without any assumption on how many workgroups are resident.  Every wait is also bounded: past the
 // limit the batch is aborted (VI_EDEVICE) and every workgroup exits.
 //
 // Back-substitution x = L^-T y is a second dataflow, over block columns:
@@ -692,7 +693,7 @@ __global__ void __launch_bounds__(64) k_chol_df(DevPlan D, int ntickets, double*
 #pragma unroll
       for (int it = 0; it < 16; ++it) {
         const int e = lane + 64 * it;
-          agent_store(Lo + e, Lt[(e >> 5) * LD + (e & 31)]);
+        agent_store(Lo + e, Lt[(e >> 5) * LD + (e & 31)]);
       }
       publish(fl + j * nblk + j);
     } else {
@@ -1019,7 +1020,7 @@ __global__ void __launch_bounds__(256) k_chol_bs(DevPlan D, int t0, int nbs, con
     const int t = tk;
     __syncthreads();
     if (t >= nbs) return;
-    // two block columns per ticket, c and c - 1 (of one chain), so that the
+    // two block columns per ticket, c and c - 1 (tile (c, c - 1) is nonzero), so that the
     // chain of the back-substitution hands over between workgroups at every
     // second block only
     const int w = D.chol_tiles[2 * (t0 + t)];
@@ -1054,8 +1055,8 @@ __global__ void __launch_bounds__(256) k_chol_bs(DevPlan D, int t0, int nbs, con
     }
     // t_c = y_c - sum_b L_bc^T x_b over b = nblk-1 .. c+1 (in that order),
     // and the same sum for column c - 1, over the nonzero tiles: the flags of up
-    // to 32 blocks are read at once (a block of a zero tile counts as ready) and every ready run is summed with one acquire and its loads in
-    // flight.  The tiles of block c + 1, whose x comes last (it waits for the
+    // to 32 blocks are read at once (a block of a zero tile counts as ready) and
+    // every ready run is summed with one acquire and its loads in flight.  The tiles of block c + 1, whose x comes last (it waits for the
     // previous ticket), are loaded before any wait: the factor is final.
     double acc = 0.0, accb = 0.0;
     double vl[4], vlb[4];

@@ -64,10 +64,9 @@ __device__ __forceinline__ double imu_grad(const double* gw, int N, int b, int c
 // coordinates of every keyframe are the one unknown in the last keyframe's
 // slot, so the folded system G^T B G sums an entry over the keyframes whose
 // bias it touches (those of the inertial factors next to the other index)
-template <bool AG = false>
 __device__ __forceinline__ double imu_hess_folded(const double* Hw, int N, int a, int ra, int b, int cb, bool global) {
   const bool ga = global && ra >= 9, gb = global && cb >= 9;
-  if (!ga && !gb) return imu_hess<AG>(Hw, N, a, ra, b, cb);
+  if (!ga && !gb) return imu_hess(Hw, N, a, ra, b, cb);
   double v = 0.0;
   if (ga && gb) {
     for (int f = 0; f < N - 1; ++f) {
@@ -75,9 +74,9 @@ __device__ __forceinline__ double imu_hess_folded(const double* Hw, int N, int a
       v += H[ra * 30 + cb] + H[ra * 30 + 15 + cb] + H[(15 + ra) * 30 + cb] + H[(15 + ra) * 30 + 15 + cb];
     }
   } else if (gb) {
-    for (int b2 = max(a - 1, 0); b2 <= min(a + 1, N - 1); ++b2) v += imu_hess<AG>(Hw, N, a, ra, b2, cb);
+    for (int b2 = max(a - 1, 0); b2 <= min(a + 1, N - 1); ++b2) v += imu_hess(Hw, N, a, ra, b2, cb);
   } else {
-    for (int a2 = max(b - 1, 0); a2 <= min(b + 1, N - 1); ++a2) v += imu_hess<AG>(Hw, N, a2, ra, b, cb);
+    for (int a2 = max(b - 1, 0); a2 <= min(b + 1, N - 1); ++a2) v += imu_hess(Hw, N, a2, ra, b, cb);
   }
   return v;
 }

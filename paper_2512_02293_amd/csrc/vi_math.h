@@ -77,7 +77,9 @@ __device__ __forceinline__ void skew(const double* w, double* S) {
 // sample lies) the dropped terms are below 2^-54 of the sum, without the
 // cancellation of 1 - cos t and t - sin t, and 7 or 8 fused operations replace
 // a square root, a sine, a cosine and divisions (some 200 instructions on the
-// serial lanes that form the inertial factors).
+// serial lanes that form the inertial factors).  The logarithm has the series of
+// the arc sine instead, in sin t, up to sin t = 1/8: beyond it the terms fall
+// too slowly.
 constexpr double kSeriesT2 = 0.25;
 __device__ __forceinline__ double series_sinc(double x) {           // sin t / t
   return 1.0 + x * (-1.0 / 6 + x * (1.0 / 120 + x * (-1.0 / 5040 + x * (1.0 / 362880 + x * (-1.0 / 39916800 +
@@ -256,9 +258,9 @@ __device__ inline void quat_retract(double* q, const double* w) {
 __device__ __forceinline__ void wave_lds_sync() { asm volatile("" ::: "memory"); }
 
 // Cholesky factor of a 9 x 9 SPD block by one wave, every lane in registers: L
-// holds the lower part packed by rows, on return the factor with 1 / L_jj in
-// rv.  Along with it each lane solves L x = v for its own v.  Returns the first
-// pivot that is not positive, or -1.
+// holds the lower part packed by rows, on return the factor below the diagonal
+// and on it the pivots L_jj^2.  Along with it each lane solves L x = v for its
+// own v.  Returns the first pivot that is not positive, or -1.
 __device__ __forceinline__ constexpr int tri9c(int i, int j) { return i * (i + 1) / 2 + j; }
 
 __device__ __forceinline__ int factor9_solve(double (&L)[46], double (&v)[9]) {
