@@ -27,10 +27,11 @@ def _fastest(fn, reps=25):
     return best
 
 
-@pytest.fixture(scope="module")
-def unit():
+def _against_sort(fn):
+    """The smallest of three ratios, each of two fastest times taken one after
+    the other, so that a busy CPU slows both or is met by another try."""
     a = np.random.default_rng(1).standard_normal(100000)
-    return _fastest(lambda: np.argsort(a, kind="stable"))
+    return min(_fastest(fn) / _fastest(lambda: np.argsort(a, kind="stable")) for _ in range(3))
 
 
 def _edges(ii, jj):
@@ -39,16 +40,16 @@ def _edges(ii, jj):
 
 
 @pytest.mark.parametrize("n,k,loops,bound", [(512, 11, 200, 0.55), (128, 6, 40, 0.055)])
-def test_trajectory(unit, n, k, loops, bound):
+def test_trajectory(n, k, loops, bound):
     prob = synth.make_problem(synth.SceneConfig(n_kf=n, H=1, W=1, k_out=k, n_loop=loops, kf_gap=20), 3)
     lib, o, cam = binding.load(), binding.make_opts(), binding.make_camera(60.0, 60.0, 32.0, 24.0, 48, 64)
     ii, jj, ed = _edges(prob.ii, prob.jj)
     size = lambda: lib.vi_workspace_size(C.byref(cam), n, C.byref(ed), C.byref(o))
     assert size() > 0
-    assert _fastest(size) < bound * unit
+    assert _against_sort(size) < bound
 
 
-def test_pose_graph(unit):
+def test_pose_graph():
     n = 512
     rng = np.random.default_rng(5)
     loops = sorted({(int(i), int(j)) for i, j in rng.integers(0, n, size=(220, 2)) if abs(int(i) - int(j)) > 50})[:200]
@@ -59,4 +60,4 @@ def test_pose_graph(unit):
     rl = binding.RelPoses(len(rel), ri.ctypes.data_as(C.c_void_p), rj.ctypes.data_as(C.c_void_p), None, None)
     size = lambda: lib.vi_pgba_workspace_size(C.byref(cam), n, C.byref(ed), C.byref(rl), C.byref(o))
     assert size() > 0
-    assert _fastest(size) < 0.2 * unit
+    assert _against_sort(size) < 0.2
